@@ -50,9 +50,8 @@
 // per group of 4 accumulator registers, 4 consecutive output features.
 //
 // The dense path is the same kernel with every tile kept and W read straight
-// from its row-major layout into the same slice layout as X.  fp32 runs a plain
-// VALU kernel over the canonical BSR arrays (it serves the small fp32
-// configuration only).
+// from its row-major layout into the same slice layout as X.  fp32 has a kernel
+// of its own over the canonical BSR arrays (k_linear_f32).
 #include "lpv_device.h"
 #include "lpv_internal.h"
 
@@ -851,10 +850,28 @@ __global__ __launch_bounds__(NT, 1) void k_linear16(
     __builtin_amdgcn_s_waitcnt(0);
 }
 
-// fp32: 64 tokens x 16 outputs per workgroup; thread = one token x 4 outputs.
-// Sparse: the 16 outputs lie in one block-row (b_r >= 16), whose kept blocks
-// are walked through row_ptr / col_idx.  Dense: every column.
-template <bool GELU, bool DENSE>
+// fp32 (v_mfma_f32_16x16x4_f32: float32 products and sums, 256 FLOP per clock
+// and CU, twice the rate of unpacked VALU multiply-adds).  A wave takes 16
+// outputs (inside one block row, b_r >= 16) times 16 T tokens and walks the
+// row's kept blocks (dense: every column) in 16-column steps.  A step's
+// operands -- 16 weight rows and 16 T token rows of 64 bytes -- go by
+// global->LDS DMA into the wave's own ring of ST stages (no barrier: only the
+// wave reads them).  The DMA lets four consecutive lanes fetch one row's 64
+// bytes, one L1 access; the matrix-core order (lane l: row l % 16) straight
+// from global memory took 60 accesses per instruction instead of 16 and ran at
+// half the speed.  Lane l then reads 16 bytes of row l % 16 at column 4 (l /
+// 16): element e feeds the e-th instruction, whose k slots are the columns
+// 4 (l / 16) + e, the same for both operands.  The 16-byte pieces of a row are
+// XOR-placed by row / 4, so 16 rows of one column lie in distinct banks.  The
+// block row's column indices sit in lanes (64 at a time): no index load is in
+// the chain.  The launcher takes the most tokens per wave (fewest operand
+// bytes per product) that still gives every SIMD two waves.  12608 tokens, 384
+// -> 1536, 16 x 16 blocks at 50%: 94 us (79 TFLOP/s; 142 us without the DMA),
+// bound by 64-byte pieces from L2; 197 tokens, 192 -> 768: 4.7 us, latency
+// (21 us with plain multiply-adds and element loads).
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+template <bool GELU, bool DENSE, int T>
 __global__ __launch_bounds__(256) void k_linear_f32(const float* __restrict__ X, int64_t ldx,
                                                     int64_t M, int64_t K, int64_t N,
                                                     const float* __restrict__ values,
@@ -865,40 +882,107 @@ __global__ __launch_bounds__(256) void k_linear_f32(const float* __restrict__ X,
                                                     const float* __restrict__ bias,
                                                     float* __restrict__ Y, int64_t ldy)
 {
-    const int64_t m = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
-    const int64_t n0 = (int64_t)blockIdx.y * 16 + (threadIdx.x >> 6) * 4;
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    const bool live = m < M;
-    const int64_t mm = live ? m : 0;
-    if (DENSE) {
-        for (int64_t k = 0; k < K; ++k) {
-            const float x = X[mm * ldx + k];
+    constexpr int ST = T == 1 ? 6 : T == 2 ? 5 : 4;  // stages of 1 + T KB per wave
+    constexpr int SU4 = (1 + T) * 64;                // 16-byte chunks of a stage
+    __shared__ uint4 smem[4 * ST * SU4];
+    const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    // workgroup L of the grid (x fastest; gridDim.x is a multiple of 8) runs on
+    // XCD L % 8: the workgroups of one token tile follow each other there, so
+    // the tile's X comes into one L2 only
+    const uint32_t idx = (uint32_t)(((uint64_t)blockIdx.y * gridDim.x + blockIdx.x) >> 3);
+    const int64_t m0 = ((int64_t)(idx / gridDim.y) * 8 + (blockIdx.x & 7)) * (16 * T);
+    const int n0 = ((int)(idx % gridDim.y) * 4 + wave) * 16;  // N is at most 65536
+    if (n0 >= N || m0 >= M)
+        return;  // (no barrier below)
+    uint4* ring = smem + wave * (ST * SU4);
+    // DMA lane: 16-byte piece dc of row lane / 4, from wave-uniform bases
+    // (tokens past M repeat the last, never stored); 32-bit byte offsets: 64
+    // rows of a leading dimension of at most 2^22
+    const int drow = lane >> 2, dc = (lane & 3) ^ (lane >> 4);
+    const char* xbase = (const char*)(X + m0 * ldx);
+    uint32_t xoff[T];
 #pragma unroll
-            for (int o = 0; o < 4; ++o)
-                acc[o] = fmaf(x, W[(n0 + o) * ldw + k], acc[o]);
+    for (int t = 0; t < T; ++t)
+        xoff[t] = (uint32_t)((min((int64_t)(16 * t + drow), M - 1 - m0) * ldx + 4 * dc) * 4);
+    const uint32_t woff = (uint32_t)((drow * (DENSE ? ldw : (int64_t)b_c) + 4 * dc) * 4);
+    const uint32_t rd = lds_addr(ring) + r * 64 + ((q ^ (r >> 2)) * 16);
+    f32x4 acc[T];
+    {
+        const f32x4 b = bias ? *(const f32x4*)(bias + n0 + 4 * q) : f32x4{};
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+            acc[t] = b;
+    }
+    // steps of 16 columns: of the whole row (dense), or of up to 64 kept
+    // blocks at a time, whose columns the lanes of `cols` hold
+    const int csh = DENSE ? 0 : __builtin_ctz(b_c) - 4;  // log2 of steps per block
+    const int br = DENSE ? 0 : n0 >> __builtin_ctz(b_r);
+    const int p_end = DENSE ? 1 : row_ptr[br + 1];
+    for (int p0 = DENSE ? 0 : row_ptr[br]; p0 < p_end; p0 += 64) {
+        int cols = 0, steps;
+        const char* wbase;
+        if (DENSE) {
+            steps = (int)(K / 16);
+            wbase = (const char*)(W + n0 * ldw);
+        } else {
+            const int n = min(p_end - p0, 64);
+            steps = n << csh;
+            cols = col_idx[p0 + min(lane, n - 1)];
+            wbase = (const char*)(values + ((int64_t)p0 * b_r + (n0 - br * b_r)) * b_c);
         }
-    } else {
-        const int r = (int)(n0 / b_r);
-        const int64_t i0 = n0 - (int64_t)r * b_r;
-        for (int p = row_ptr[r]; p < row_ptr[r + 1]; ++p) {
-            const int64_t kc = (int64_t)col_idx[p] * b_c;
-            const float* blk = values + (int64_t)p * b_r * b_c;
-            for (int kk = 0; kk < b_c; ++kk) {
-                const float x = X[mm * ldx + kc + kk];
-#pragma unroll
-                for (int o = 0; o < 4; ++o)
-                    acc[o] = fmaf(x, blk[(i0 + o) * b_c + kk], acc[o]);
+        auto dma = [&](int s, int slot) {
+            uint4* dst = ring + slot * SU4;
+            int64_t c = (int64_t)s * 16, wc = c;
+            if (!DENSE) {
+                const int p = s >> csh, sub = (s - (p << csh)) * 16;
+                c = (int64_t)__builtin_amdgcn_readlane(cols, p) * b_c + sub;
+                wc = (int64_t)p * b_r * b_c + sub;
             }
+            dma16(wbase + wc * 4, woff, dst);
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+                dma16(xbase + c * 4, xoff[t], dst + (1 + t) * 64);
+        };
+        int slot = 0;
+        for (int s = 0; s < min(ST, steps); ++s)
+            dma(s, s);
+        for (int s = 0; s < steps; ++s) {
+            // this step's DMA has landed (the later steps' may be in flight;
+            // nothing else of this wave is)
+            if (s + ST <= steps)
+                asm volatile("s_waitcnt vmcnt(%0)" ::"i"((ST - 1) * (1 + T)) : "memory");
+            else
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            const uint32_t at = rd + (uint32_t)slot * (SU4 * 16);
+            const f32x4 w = __builtin_bit_cast(f32x4, lds_read16<0>(at));
+            f32x4 x[T];
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+                x[t] = __builtin_bit_cast(f32x4, lds_read16<0>(at + (1 + t) * 1024));
+            // the stage is read: it may be filled again
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (s + ST < steps)
+                dma(s + ST, slot);
+            slot = slot + 1 == ST ? 0 : slot + 1;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int t = 0; t < T; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[e], x[t][e], acc[t], 0, 0, 0);
         }
     }
-    if (!live)
-        return;
+    // lane l holds outputs 4 (l / 16) .. + 3 of token l % 16
 #pragma unroll
-    for (int o = 0; o < 4; ++o) {
-        float v = acc[o] + (bias ? bias[n0 + o] : 0.0f);
-        if (GELU)
-            v = gelu_erf(v);
-        Y[m * ldy + n0 + o] = v;
+    for (int t = 0; t < T; ++t) {
+        const int64_t m = m0 + 16 * t + r;
+        if (GELU) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                acc[t][i] = gelu_erf(acc[t][i]);
+        }
+        if (m < M)
+            *(f32x4*)(Y + m * ldy + n0 + 4 * q) = acc[t];
     }
 }
 
@@ -1057,17 +1141,33 @@ hipError_t launch_f32(bool gelu, const float* X, int64_t ldx, int64_t M, int64_t
                       const lpv_bsr* h, const float* W, int64_t ldw, const float* bias, float* Y,
                       int64_t ldy, hipStream_t s)
 {
-    const dim3 grid((unsigned)((M + 63) / 64), (unsigned)(N / 16)), block(256);
     const float* vals = h ? (const float*)h->values : nullptr;
     const int32_t* rp = h ? h->row_ptr : nullptr;
     const int32_t* ci = h ? h->col_idx : nullptr;
     const int32_t b_r = h ? h->b_r : 16, b_c = h ? h->b_c : 16;
+    // 16 T tokens per wave: the largest T that leaves two waves for every SIMD
+    const int64_t rows = N / 16, want = (int64_t)num_cus() * 8;
+    const int T = rows * ((M + 63) / 64) >= want ? 4 : rows * ((M + 31) / 32) >= want ? 2 : 1;
+    const dim3 grid((unsigned)(((M + 16 * T - 1) / (16 * T) + 7) / 8 * 8), (unsigned)((rows + 3) / 4)),
+        block(256);
+#define LPV_F32(GELU_, T_)                                                                        \
+    hipLaunchKernelGGL((k_linear_f32<GELU_, DENSE, T_>), grid, block, 0, s, X, ldx, M, K, N, vals, \
+                       rp, ci, b_r, b_c, W, ldw, bias, Y, ldy)
+#define LPV_F32_T(GELU_)        \
+    do {                        \
+        if (T == 4)             \
+            LPV_F32(GELU_, 4);  \
+        else if (T == 2)        \
+            LPV_F32(GELU_, 2);  \
+        else                    \
+            LPV_F32(GELU_, 1);  \
+    } while (0)
     if (gelu)
-        hipLaunchKernelGGL((k_linear_f32<true, DENSE>), grid, block, 0, s, X, ldx, M, K, N, vals,
-                           rp, ci, b_r, b_c, W, ldw, bias, Y, ldy);
+        LPV_F32_T(true);
     else
-        hipLaunchKernelGGL((k_linear_f32<false, DENSE>), grid, block, 0, s, X, ldx, M, K, N, vals,
-                           rp, ci, b_r, b_c, W, ldw, bias, Y, ldy);
+        LPV_F32_T(false);
+#undef LPV_F32_T
+#undef LPV_F32
     return hipGetLastError();
 }
 

@@ -63,6 +63,24 @@ def test_parity_fp32_blocks(b_r, b_c):
     assert_close(f64(Y), ref(w), "f32", w.name)
 
 
+@pytest.mark.parametrize("M,N,K,b_r,b_c", [
+    (1, 16, 16, 16, 16),        # one step, one token
+    (17, 80, 48, 16, 16),       # token tail; 5 row tiles (not a multiple of the 4 waves)
+    (65, 64, 1104, 16, 16),     # 69 blocks a row: a second run of column indices
+    (1000, 1664, 64, 32, 64),   # 32 tokens per wave
+    (2049, 1024, 192, 64, 32),  # 64 tokens per wave, a tail of one
+])
+def test_fp32_tiles(M, N, K, b_r, b_c):
+    # (the bar of 1e-5 covers float32 sums of up to 1104 products)
+    w = wl.custom(41, M, N, K, b_r, b_c, "f32", "all" if K > 1000 else "uniform", 40)
+    say("fp32 tiles", M, N, K, b_r, b_c)
+    _, Y = run_bsr(w)
+    assert_close(f64(Y), ref(w), "f32", w.name)
+    Yd = lpv.dense_linear(dev(w.W, "f32"), dev(w.X, "f32"), dev(w.bias, "f32"))
+    r = oracle.linear(w.X, w.W, "f32", w.b_r, w.b_c, np.ones_like(w.mask), w.bias)
+    assert_close(f64(Yd), r, "f32", "dense")
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
 @pytest.mark.parametrize("b_r,b_c", [(16, 16), (32, 32), (64, 32)])
 def test_exact_small_integers(dtype, b_r, b_c):
