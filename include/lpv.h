@@ -244,8 +244,9 @@ lpv_status lpv_bsr_transpose(const lpv_bsr* h, void* stream, lpv_bsr** out);
  *         the BSR value order of lpv_bsr_export (block-rows ascending, kept
  *         columns ascending, each block row-major).
  * Sums run in float32 over fixed token chunks added in a fixed order, one
- * rounding at the end.  16-bit types use the matrix cores; fp32 handles a
- * plain kernel.  The partial sums of the kept tiles per token chunk live in a
+ * rounding at the end.  16-bit types use the 16-bit matrix instructions,
+ * fp32 handles the float32 ones (no workspace: the chunks meet inside a
+ * workgroup).  The 16-bit partial sums of the kept tiles per token chunk live in a
  * workspace the handle owns: allocated on the handle's first 16-bit call
  * (chunks x kept tiles x 4 KiB, the chunk count fixed per handle by the
  * device's compute-unit count) and freed by lpv_bsr_destroy, so later calls

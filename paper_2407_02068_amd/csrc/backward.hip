@@ -7,8 +7,8 @@
 // Z = X W~^T + b and G = dL/dZ (M x N):
 //   dX = G W~         the forward kernel run on the handle of W~^T, which
 //                     k_transpose_blocks + pack build (lpv_bsr_transpose)
-//   dW = G^T X        on the kept blocks only: k_gradw_tiles (matrix cores)
-//                     and k_gradw_reduce, or k_gradw_plain for fp32 handles
+//   dW = G^T X        on the kept blocks only: k_gradw_tiles and
+//                     k_gradw_reduce, or k_gradw_f32 for fp32 handles
 //   db = sum_m G[m]   k_bias_partial + k_bias_reduce
 // Every sum is taken in a fixed order, so results do not depend on timing.
 #include <mutex>
@@ -167,26 +167,174 @@ __device__ inline int block_row(const int32_t* row_ptr, int R, int64_t p)
     return lo;
 }
 
-// One workgroup per kept block; each thread sums whole elements over all
-// tokens, ascending.  For fp32 handles (small layers).
-template <int DT>
-__global__ __launch_bounds__(256) void k_gradw_plain(int32_t b_r, int32_t b_c, int32_t R,
-                                                     const int32_t* __restrict__ row_ptr,
-                                                     const int32_t* __restrict__ col_idx,
-                                                     const char* __restrict__ G, int64_t ldg,
-                                                     const char* __restrict__ X, int64_t ldx,
-                                                     int64_t M, char* __restrict__ out)
+__device__ inline uint32_t lds_u32(const void* p)
 {
-    const int64_t p = blockIdx.x;
+    return (uint32_t)(uintptr_t)((const __attribute__((address_space(3))) char*)p);
+}
+
+// 16 bytes per lane from a per-lane global address into LDS at M0 + 16 lane.
+__device__ inline void gw_dma(const void* src, uint32_t m0)
+{
+    asm volatile(
+        "s_nop 0\n"
+        "global_load_lds_dwordx4 %0, off"
+        :
+        : "v"(src), "{m0}"(m0)
+        : "memory");
+}
+
+// The same from a wave-uniform base (saddr) and a per-lane 32-bit offset.
+__device__ inline void gw_dma_off(const char* base, uint32_t off, uint32_t m0)
+{
+    asm volatile(
+        "s_nop 0\n"
+        "global_load_lds_dwordx4 %0, %1"
+        :
+        : "v"(off), "s"(base), "{m0}"(m0)
+        : "memory");
+}
+
+// A workgroup takes one sub-tile of 16 VR x 16 VC elements of a kept block;
+// its 8 waves take runs of 16 tokens in turn, four v_mfma_f32_16x16x4_f32
+// (float32 products and sums) per run and 16 x 16 elements.  A run's pieces of
+// G and X rows (64 VR and 64 VC bytes) go by global->LDS DMA into the wave's
+// own ring of GWF_ST stages (no barrier: only the wave reads them); lane l
+// reads VR (VC) neighbouring columns of token 4 k + l / 16 for the k-th product,
+// at 256 VR consecutive bytes for the wave, and element e of them is row (column)
+// V (l % 16) + e of the sub-tile.  The waves' sums are added in wave order in
+// LDS: no workspace, a fixed order.  Loads of single elements straight into
+// registers took four times the vector-memory instructions, with too few bytes in
+// flight.  3152 tokens, 768 x 192, 288 16 x 16 blocks: 21 us (34 us with register
+// loads; 773 us with one thread per element, serial over the tokens), bound by
+// the 64-byte pieces of G and X that every block reads from L2.
+constexpr int GWF_WAVES = 8;
+constexpr int GWF_ST = 4;
+typedef float gwf_x4 __attribute__((ext_vector_type(4)));
+typedef float gwf_x2 __attribute__((ext_vector_type(2)));
+
+template <int V> __device__ inline void gwf_read(uint32_t addr, float* v)
+{
+    if constexpr (V == 1) {
+        v[0] = *(const __attribute__((address_space(3))) float*)(uintptr_t)addr;
+    } else {
+        const gwf_x2 t = *(const __attribute__((address_space(3))) gwf_x2*)(uintptr_t)addr;
+        v[0] = t[0];
+        v[1] = t[1];
+    }
+}
+
+template <int VR, int VC>
+__global__ __launch_bounds__(64 * GWF_WAVES) void k_gradw_f32(int32_t b_r, int32_t b_c, int32_t R,
+                                                              const int32_t* __restrict__ row_ptr,
+                                                              const int32_t* __restrict__ col_idx,
+                                                              const float* __restrict__ G, int64_t ldg,
+                                                              const float* __restrict__ X, int64_t ldx,
+                                                              int64_t M, int64_t tiles,
+                                                              float* __restrict__ out)
+{
+    constexpr int SB = (VR + VC) * 1024;  // bytes of a stage: 16 tokens of G, then of X
+    constexpr int RING = GWF_WAVES * GWF_ST * SB;
+    static_assert(GWF_WAVES * VR * VC * 1024 <= RING, "the waves' sums fit in the rings");
+    __shared__ uint4 smem[RING / 16];
+    // sub-tiles in BSR order, a contiguous run to each XCD (workgroup b runs on
+    // XCD b % 8): an XCD's L2 then holds the G columns of its block rows
+    const int scsh = __builtin_ctz(b_c / (16 * VC)), subsh = __builtin_ctz(b_r / (16 * VR)) + scsh;
+    const int64_t item = (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (item >= tiles)
+        return;  // (the whole workgroup)
+    const int64_t p = item >> subsh;
+    const int sub = (int)(item - (p << subsh));
+    const int i0 = (sub >> scsh) * (16 * VR);              // in the block
+    const int j0 = (sub & ((1 << scsh) - 1)) * (16 * VC);
     const int r = block_row(row_ptr, R, p), c = col_idx[p];
-    const int nb = b_r * b_c;
-    for (int e = threadIdx.x; e < nb; e += 256) {
-        const int i = e / b_c, j = e - i * b_c;
-        const int64_t n = (int64_t)r * b_r + i, k = (int64_t)c * b_c + j;
-        float acc = 0.0f;
-        for (int64_t m = 0; m < M; ++m)
-            acc += load_elem<DT>(G, m * ldg + n) * load_elem<DT>(X, m * ldx + k);
-        store_elem<DT>(out, p * nb + e, acc);
+    const int lane = threadIdx.x & 63, l16 = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const char* gp = (const char*)(G + (int64_t)r * b_r + i0);
+    const char* xp = (const char*)(X + (int64_t)c * b_c + j0);
+    // DMA instruction i of a part (V = VR or VC of them): tokens 16 / V i ..,
+    // lane: token lane / (4 V), 16-byte piece lane % (4 V); 32-bit byte offsets
+    // (16 rows of a leading dimension of at most 2^22)
+    const int grow = lane / (4 * VR), xrow = lane / (4 * VC);
+    const uint32_t gco = (lane % (4 * VR)) * 16, xco = (lane % (4 * VC)) * 16;
+    const uint32_t ring = lds_u32(smem) + (uint32_t)wave * (GWF_ST * SB);
+    auto dma = [&](int64_t run, int slot) {
+        const int64_t m0 = run * 16;
+        const int last = (int)min((int64_t)15, M - 1 - m0);  // rows past M repeat the last
+        const char* gb = gp + m0 * ldg * 4;
+        const char* xb = xp + m0 * ldx * 4;
+        const uint32_t dst = ring + (uint32_t)slot * SB;
+#pragma unroll
+        for (int i = 0; i < VR; ++i)
+            gw_dma_off(gb, (uint32_t)(min(16 / VR * i + grow, last) * ldg * 4) + gco, dst + i * 1024);
+#pragma unroll
+        for (int i = 0; i < VC; ++i)
+            gw_dma_off(xb, (uint32_t)(min(16 / VC * i + xrow, last) * ldx * 4) + xco,
+                       dst + (VR + i) * 1024);
+    };
+    gwf_x4 acc[VR][VC] = {};
+    const int64_t runs = (M + 15) / 16;
+    const int64_t n = runs > wave ? (runs - wave + GWF_WAVES - 1) / GWF_WAVES : 0;  // this wave's
+    for (int k = 0; k < GWF_ST && k < n; ++k)
+        dma(wave + (int64_t)k * GWF_WAVES, k);
+    int slot = 0;
+    for (int64_t k = 0; k < n; ++k) {
+        if (k + GWF_ST <= n)
+            asm volatile("s_waitcnt vmcnt(%0)" ::"i"((GWF_ST - 1) * (VR + VC)) : "memory");
+        else
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const uint32_t at = ring + (uint32_t)slot * SB;
+        float g[4][VR], x[4][VC];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            gwf_read<VR>(at + (4 * e + q) * (64 * VR) + l16 * (4 * VR), g[e]);
+            gwf_read<VC>(at + VR * 1024 + (4 * e + q) * (64 * VC) + l16 * (4 * VC), x[e]);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the stage may be filled again
+        if (k + GWF_ST < n)
+            dma(wave + (k + GWF_ST) * GWF_WAVES, slot);
+        slot = (slot + 1) % GWF_ST;
+        const int64_t m0 = (wave + k * GWF_WAVES) * 16;
+        if (m0 + 16 > M) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (m0 + 4 * e + q >= M) {
+                    for (float& v : g[e])
+                        v = 0.0f;
+                    for (float& v : x[e])
+                        v = 0.0f;
+                }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int a = 0; a < VR; ++a)
+#pragma unroll
+                for (int b = 0; b < VC; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(g[e][a], x[e][b], acc[a][b], 0, 0, 0);
+    }
+    // (no DMA is in flight: each wave's last wait was for all of its own)
+    __syncthreads();
+    gwf_x4* s_sum = (gwf_x4*)smem;  // [wave][a VC + b][lane]
+#pragma unroll
+    for (int a = 0; a < VR; ++a)
+#pragma unroll
+        for (int b = 0; b < VC; ++b)
+            s_sum[(wave * VR * VC + a * VC + b) * 64 + lane] = acc[a][b];
+    __syncthreads();
+    // product (a, b): lane l, register i is row VR (4 (l / 16) + i) + a, column
+    // VC (l % 16) + b of the sub-tile
+    for (int e = threadIdx.x; e < VR * VC * 64; e += 64 * GWF_WAVES) {
+        const int ab = e >> 6, ln = e & 63;
+        gwf_x4 s = s_sum[e];
+#pragma unroll
+        for (int w = 1; w < GWF_WAVES; ++w)
+            s += s_sum[w * VR * VC * 64 + e];
+        const int j = j0 + VC * (ln & 15) + ab % VC;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int row = i0 + VR * (4 * (ln >> 4) + i) + ab / VC;
+            out[(p * b_r + row) * b_c + j] = s[i];
+        }
     }
 }
 
@@ -229,33 +377,6 @@ struct GradWDims {
 };
 
 __device__ inline int gw_swz(int row) { return (row & 3) | ((row >> 1) & 4); }
-
-__device__ inline uint32_t lds_u32(const void* p)
-{
-    return (uint32_t)(uintptr_t)((const __attribute__((address_space(3))) char*)p);
-}
-
-// 16 bytes per lane from a per-lane global address into LDS at M0 + 16 lane.
-__device__ inline void gw_dma(const void* src, uint32_t m0)
-{
-    asm volatile(
-        "s_nop 0\n"
-        "global_load_lds_dwordx4 %0, off"
-        :
-        : "v"(src), "{m0}"(m0)
-        : "memory");
-}
-
-// The same from a wave-uniform base (saddr) and a per-lane 32-bit offset.
-__device__ inline void gw_dma_off(const char* base, uint32_t off, uint32_t m0)
-{
-    asm volatile(
-        "s_nop 0\n"
-        "global_load_lds_dwordx4 %0, %1"
-        :
-        : "v"(off), "s"(base), "{m0}"(m0)
-        : "memory");
-}
 
 typedef short v4s __attribute__((ext_vector_type(4)));
 
@@ -677,9 +798,28 @@ hipError_t launch_grad_w(const lpv_bsr* h, const GradWCall& c, hipStream_t s)
         return hipMemsetAsync(c.dW, 0, (size_t)total * (h->dtype == LPV_F32 ? 4 : 2), s);
     }
     if (h->dtype == LPV_F32) {
-        hipLaunchKernelGGL(k_gradw_plain<LPV_F32>, dim3((unsigned)h->nnzb), dim3(256), 0, s, h->b_r,
-                           h->b_c, h->R, (const int32_t*)h->row_ptr, (const int32_t*)h->col_idx,
-                           (const char*)c.G, c.ldg, (const char*)c.X, c.ldx, c.M, (char*)c.dW);
+        // 32-wide sub-tiles halve the operand reads per product (and read whole
+        // 128-byte lines) but make a quarter of the workgroups: taken when they
+        // give every CU one.  12608 tokens, 1536 x 384, 288 32 x 32 blocks: 134 us against
+        // 172 us with 16-wide ones.
+        const int64_t t32 = h->nnzb * (int64_t)((h->b_r + 31) / 32) * ((h->b_c + 31) / 32);
+        const bool wide = t32 >= (int64_t)device_cus();
+        const int vr = wide && h->b_r >= 32 ? 2 : 1, vc = wide && h->b_c >= 32 ? 2 : 1;
+        const int64_t tiles = total / (256 * vr * vc);
+        const dim3 grid((unsigned)((tiles + 7) / 8 * 8)), block(64 * GWF_WAVES);  // (at most 2^24 sub-tiles)
+#define LPV_GWF(VR_, VC_)                                                                          \
+    hipLaunchKernelGGL((k_gradw_f32<VR_, VC_>), grid, block, 0, s, h->b_r, h->b_c, h->R,           \
+                       (const int32_t*)h->row_ptr, (const int32_t*)h->col_idx, (const float*)c.G,  \
+                       c.ldg, (const float*)c.X, c.ldx, c.M, tiles, (float*)c.dW)
+        if (vr == 2 && vc == 2)
+            LPV_GWF(2, 2);
+        else if (vr == 2)
+            LPV_GWF(2, 1);
+        else if (vc == 2)
+            LPV_GWF(1, 2);
+        else
+            LPV_GWF(1, 1);
+#undef LPV_GWF
         return hipGetLastError();
     }
     GradWDims d = {};

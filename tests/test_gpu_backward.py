@@ -87,6 +87,19 @@ def test_backward_fp32():
     check_all(w, G, "fp32 tiny")
 
 
+@pytest.mark.parametrize("M", [1, 5, 255, 256, 259])
+@pytest.mark.parametrize("N,K,b_r,b_c", [
+    (64, 96, 32, 16),      # few blocks: 16 x 16 sub-tiles
+    (1024, 1024, 64, 32),  # 32 x 32 sub-tiles
+    (512, 512, 16, 32),    # 16 x 32 (512 blocks)
+    (512, 512, 32, 16),    # 32 x 16
+])
+def test_backward_fp32_tiles(M, N, K, b_r, b_c):
+    # token groups of 4, batches of 8 groups per wave, 8 waves: 256 tokens a batch
+    w, G = case(M, N, K, b_r, b_c, "f32", "all", cfg=97)
+    check_all(w, G, "fp32 tiles")
+
+
 def test_backward_m0():
     w, G = case(4, 256, 256, 32, 32, "bf16", cfg=95)
     h = lpv.bsr_pack(dev(w.W, "bf16"), dev(w.mask), 32, 32)
