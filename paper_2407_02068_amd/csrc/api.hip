@@ -184,9 +184,10 @@ lpv_status lpv_bsr_pack(const void* W, int64_t ldw, int64_t N, int64_t K, lpv_dt
     h->n_groups = (h->n_tile_rows + lpv::GROUP_TILES - 1) / lpv::GROUP_TILES;
     hipStream_t s = (hipStream_t)stream;
 
-    // one buffer for gdesc (16-byte entries first), row_ptr, group_order,
-    // step_ptr, group_tile0 and the plan
-    const size_t n_meta = 4 * (size_t)h->n_groups + (size_t)(h->R + 1) +
+    // one buffer for gdesc (16-byte entries first), half_tiles, row_ptr,
+    // group_order, step_ptr, group_tile0 and the plan
+    const size_t n_half = (size_t)2 * h->n_groups * (size_t)((h->n_tile_cols + 1) & ~1);
+    const size_t n_meta = 4 * (size_t)h->n_groups + n_half + (size_t)(h->R + 1) +
                           3 * (size_t)(h->n_groups + 1) + 4;
     void* meta = nullptr;
     hipError_t e = dmalloc(&meta, n_meta * sizeof(int32_t));
@@ -202,7 +203,8 @@ lpv_status lpv_bsr_pack(const void* W, int64_t ldw, int64_t N, int64_t K, lpv_dt
         return hip_fail(e, "hipGetDevice");
     }
     h->gdesc = (int4*)meta;
-    h->row_ptr = (int32_t*)(h->gdesc + h->n_groups);
+    h->half_tiles = (uint32_t*)(h->gdesc + h->n_groups);
+    h->row_ptr = (int32_t*)(h->half_tiles + n_half);
     h->group_order = h->row_ptr + (h->R + 1);
     h->step_ptr = h->group_order + (h->n_groups + 1);
     h->group_tile0 = h->step_ptr + (h->n_groups + 1);

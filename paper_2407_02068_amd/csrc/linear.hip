@@ -850,6 +850,300 @@ __global__ __launch_bounds__(NT, 1) void k_linear16(
     __builtin_amdgcn_s_waitcnt(0);
 }
 
+// ---------------------------------------------------------------- reduction split over waves
+
+// bf16 / fp16 for few token tiles (see use_split): a workgroup takes 64 tokens
+// times RT tile rows (RT divides a group's 8) and its WV waves share the
+// reduction: wave w walks every WV-th pair of column tiles (64 columns, whole
+// 128-byte lines of X) that any of the RT rows keeps, for all 64 tokens and RT
+// rows, so no operand is fetched twice in the workgroup and the main loop has no
+// barrier.  A step -- 64 rows of 128 bytes of X and the kept W tiles -- goes by
+// DMA into the wave's own LDS stage, is read into registers, and while its
+// products run the next step is on its way into the same stage; the other waves
+// of the SIMD cover what is left of the round trip.  At the end the waves'
+// float32 partial sums meet in LDS and are added in wave order; each wave finishes
+// an equal share (bias, GELU, one rounding) and the tile leaves through LDS in
+// whole rows.
+//
+// k_linear16's 256 x 256 items leave most of the chip idle when there are
+// fewer of them than CUs, and a lone item still takes a barrier and a DMA round
+// trip per pair of columns.  Bound: L2 -> LDS traffic (a step moves 8 KB of X and
+// 4 KB per kept row pair for 16 products per row) and the round trips left.
+// 197 tokens, 768 -> 3072, 50%, GELU: 6.0 us of GPU time (25.6 with
+// k_linear16); 1576 tokens, 3072 -> 768: 21 us (54).
+struct SplitDims {
+    int64_t ldx, M, K, N, ldw, ldy;
+    int32_t n_tile_rows, n_pairs;
+    int32_t n_mt, n_rb;  // token tiles of 64, row blocks of RT tile rows
+    int32_t xcd_tiles;   // 1: all row blocks of a token tile on one XCD
+};
+constexpr int SPL_BM = 64;          // tokens per workgroup
+constexpr int SPL_MAX_PAIRS = 128;  // column pairs (K at most 8192)
+
+template <int DT, bool GELU, bool DENSE, int RT, int WV>
+__global__ __launch_bounds__(64 * WV) void k_linear16_split(
+    const SplitDims a, const char* __restrict__ X, const char* __restrict__ stream,
+    const uint32_t* __restrict__ half_tiles, const char* __restrict__ W, const char* __restrict__ bias, char* __restrict__ Y)
+{
+    using E = Elem<DT>;
+    using F = typename E::frag;
+    constexpr int WOFF = 8192;               // bytes of a stage's X part
+    constexpr int SB = WOFF + RT * 4096;     // bytes of a stage: X rows, then W tiles
+    constexpr int RING = WV * SB;
+    constexpr int QN = RT * 8, QW = QN / WV; // 4-register runs of the accumulators; per finishing wave
+    constexpr int OS = RT * 64 + 16;         // bytes per token of the output tile in LDS
+    constexpr int ROUND = RING / (WV * 1024) < QN ? RING / (WV * 1024) : QN;
+    static_assert(SPL_BM * OS <= RING && QN % WV == 0, "the epilogue reuses the stages");
+    __shared__ uint4 smem[RING / 16];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // item order: workgroup b runs on XCD b % 8
+    int mt, rb_i;
+    if (a.xcd_tiles) {
+        const int idx = (int)(blockIdx.x >> 3);
+        mt = idx / a.n_rb * 8 + (int)(blockIdx.x & 7);
+        rb_i = idx % a.n_rb;
+    } else {
+        mt = (int)(blockIdx.x % (unsigned)a.n_mt);
+        rb_i = (int)(blockIdx.x / (unsigned)a.n_mt);
+    }
+    if (mt >= a.n_mt)
+        return;  // (the whole workgroup)
+    const int64_t m0 = (int64_t)mt * SPL_BM;
+    const int j0 = rb_i * RT;  // first tile row
+
+    // Lane l holds column pair l (and 64 + l) of these RT rows: per column tile the
+    // kept rows << 28 and the first kept tile.  The kept pairs, in order, are
+    // dealt to the waves in turn; todo[] is this wave's share.
+    uint32_t lt[2][2] = {};
+    uint64_t todo[2];
+    int seen = 0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int pair = 64 * h + lane;
+        if (pair < a.n_pairs) {
+            if (DENSE) {
+                lt[h][0] = lt[h][1] = (uint32_t)((1 << min(RT, a.n_tile_rows - j0)) - 1) << 28;
+            } else {
+                const uint2 v = *(const uint2*)(half_tiles + ((int64_t)(j0 / 4) * a.n_pairs + pair) * 2);
+                const int sub = RT < 4 ? j0 % 4 : 0;  // these rows' place among the table's four
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const uint32_t e = c ? v.y : v.x, bits = e >> 28;
+                    lt[h][c] = ((e & 0xfffffff) + __popc(bits & ((1u << sub) - 1))) |
+                               ((bits >> sub) & ((1u << RT) - 1)) << 28;
+                }
+            }
+        }
+        const bool kept = ((lt[h][0] | lt[h][1]) >> 28) != 0;
+        const uint64_t all = __ballot(kept);
+        todo[h] = __ballot(kept && (seen + lanes_below(all)) % WV == wave);
+        seen += __popcll(all);
+    }
+    struct Step {
+        int pair, rb;  // kept rows of the first column tile, of the second << RT
+        uint32_t t[2]; // first kept tile of either
+    };
+    auto next = [&](Step& st) -> bool {  // this wave's next pair; false after the last
+        if ((todo[0] | todo[1]) == 0)
+            return false;
+        const bool hi = todo[0] == 0;
+        uint64_t& m = hi ? todo[1] : todo[0];
+        const int l = __builtin_ctzll(m);
+        m &= m - 1;
+        const uint32_t e0 = __builtin_amdgcn_readlane(hi ? lt[1][0] : lt[0][0], l);
+        const uint32_t e1 = __builtin_amdgcn_readlane(hi ? lt[1][1] : lt[0][1], l);
+        st.pair = l + (hi ? 64 : 0);
+        st.rb = (int)(e0 >> 28 | e1 >> 28 << RT);
+        st.t[0] = e0 & 0xfffffff;
+        st.t[1] = e1 & 0xfffffff;
+        return true;
+    };
+
+    // DMA lanes: instruction i fetches rows 8 i + lane / 8, 16-byte piece dc of
+    // the row's 128 bytes (placed as in k_linear16: piece ch of row r at ch ^
+    // xswz(r)); rows past M (dense W: past N) repeat the last
+    const int drow = lane >> 3, dl = lane & 7;
+    const char* xbase = X + m0 * a.ldx * 2;
+    uint32_t xoff[8], woff[DENSE ? 4 * RT : 1];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int row = 8 * i + drow;
+        xoff[i] = (uint32_t)((min((int64_t)row, a.M - 1 - m0) * a.ldx + 8 * (dl ^ xswz(row))) * 2);
+    }
+    const char* wbase = DENSE ? W + (int64_t)j0 * TILE * a.ldw * 2 : stream;
+    if (DENSE) {
+        const int64_t wlast = a.N - 1 - (int64_t)j0 * TILE;
+#pragma unroll
+        for (int i = 0; i < 4 * RT; ++i) {
+            const int row = 8 * i + drow;
+            woff[i] = (uint32_t)((min((int64_t)row, wlast) * a.ldw + 8 * (dl ^ xswz(row))) * 2);
+        }
+    } else {
+        woff[0] = (uint32_t)lane * 16;
+    }
+    const uint32_t stage = lds_addr(smem) + (uint32_t)wave * SB;
+    auto dma = [&](const Step& st) {
+        const char* xb = xbase + st.pair * (2 * TILE * 2);
+        dma16i<0>(xb, xoff[0], stage);
+        dma16i<1024>(xb - 1024, xoff[1], stage);
+        dma16i<2048>(xb - 2048, xoff[2], stage);
+        dma16i<3072>(xb - 3072, xoff[3], stage);
+        dma16i<0>(xb, xoff[4], stage + 4096);
+        dma16i<1024>(xb - 1024, xoff[5], stage + 4096);
+        dma16i<2048>(xb - 2048, xoff[6], stage + 4096);
+        dma16i<3072>(xb - 3072, xoff[7], stage + 4096);
+        if (DENSE) {
+            const char* wb = wbase + st.pair * (2 * TILE * 2);
+#pragma unroll
+            for (int j = 0; j < RT; ++j)
+                if ((st.rb >> j) & 1) {
+                    const uint32_t at = stage + WOFF + j * 4096;
+                    dma16i<0>(wb, woff[4 * j], at);
+                    dma16i<1024>(wb - 1024, woff[4 * j + 1], at);
+                    dma16i<2048>(wb - 2048, woff[4 * j + 2], at);
+                    dma16i<3072>(wb - 3072, woff[4 * j + 3], at);
+                }
+        } else {
+            // a column's kept tiles follow each other in the stream (of fewer
+            // than 2^21 tiles: the offset fits 32 bits)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                uint32_t off = woff[0] + st.t[c] * 2048u;
+#pragma unroll
+                for (int j = 0; j < RT; ++j)
+                    if ((st.rb >> (c * RT + j)) & 1) {
+                        const uint32_t at = stage + WOFF + (c * RT + j) * 2048;
+                        dma16i<0>(wbase, off, at);
+                        dma16i<1024>(wbase, off, at);
+                        off += 2048;
+                    }
+            }
+        }
+    };
+    // fragment addresses: X and dense W, row lane % 32 (+ 32: + 4 KB), piece
+    // 2 ks + lane / 32 (k-step ks = 0..3 of the pair); sparse W tiles are in
+    // operand order
+    const int fr = lane & 31, fh = lane >> 5;
+    uint32_t xa[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+        xa[ks] = stage + fr * 128 + ((2 * ks + fh) ^ xswz(fr)) * 16;
+    const uint32_t wa = stage + WOFF + lane * 16;
+    f32x16 acc[RT][2];
+#pragma unroll
+    for (int j = 0; j < RT; ++j)
+        acc[j][0] = acc[j][1] = f32x16{};
+    Step st;
+    bool more = next(st);
+    if (more)
+        dma(st);
+    while (more) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const int rb = st.rb;
+        v4i x[4][2], w[4][RT];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            x[ks][0] = lds_read16<0>(xa[ks]);
+            x[ks][1] = lds_read16<4096>(xa[ks]);
+            // (a dropped tile's place holds stale data that no product uses)
+#pragma unroll
+            for (int j = 0; j < RT; ++j)
+                w[ks][j] = DENSE ? lds_read16<0>(xa[ks] + WOFF + j * 4096)
+                                 : lds_read16<0>(wa + ((ks >> 1) * RT + j) * 2048 + (ks & 1) * 1024);
+        }
+        // the stage is read: the next step may land in it
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        more = next(st);
+        if (more)
+            dma(st);
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int j = 0; j < RT; ++j)
+                if ((rb >> (c * RT + j)) & 1) {
+#pragma unroll
+                    for (int ks = 2 * c; ks < 2 * c + 2; ++ks) {
+                        const F wf = __builtin_bit_cast(F, w[ks][j]);
+                        acc[j][0] = E::mma(wf, __builtin_bit_cast(F, x[ks][0]), acc[j][0]);
+                        acc[j][1] = E::mma(wf, __builtin_bit_cast(F, x[ks][1]), acc[j][1]);
+                    }
+                }
+    }
+
+    // ---- epilogue, in rounds of ROUND 4-register runs (= 4 outputs of a token per
+    // lane) that the stages can hold: every wave writes its partial sums of the
+    // round, then the round's runs are dealt to the waves, which add them up in
+    // wave order
+    const uint32_t part = lds_addr(smem) + lane * 16;
+    float out[QW][4];
+#pragma unroll
+    for (int r0 = 0; r0 < QN; r0 += ROUND) {
+        __syncthreads();  // (no DMA is in flight: each wave waited for all of its own)
+#pragma unroll
+        for (int i = 0; i < ROUND; ++i) {
+            const int qi = r0 + i;
+            const f32x16& s = acc[qi / 8][(qi / 4) & 1];
+            v4i v;
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+                v[b] = __builtin_bit_cast(int, (float)s[4 * (qi & 3) + b]);
+            lds_write16(part + (uint32_t)(wave * ROUND + i) * 1024, v);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int y = 0; y < ROUND / WV; ++y) {
+            const int x = r0 / WV + y, i = y * WV + wave;
+#pragma unroll
+            for (int w = 0; w < WV; ++w) {
+                const v4i v = lds_read16<0>(part + (uint32_t)(w * ROUND + i) * 1024);
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const float f = __builtin_bit_cast(float, (int)v[b]);
+                    out[x][b] = w == 0 ? f : out[x][b] + f;
+                }
+            }
+        }
+    }
+    // run qi = WV x + wave: outputs 32 (qi / 8) + 8 (qi % 4) + 4 (lane / 32) + b
+    // of token 32 ((qi / 4) % 2) + lane % 32
+#pragma unroll
+    for (int x = 0; x < QW; ++x) {
+        const int qi = WV * x + wave;
+        const int64_t n = (int64_t)j0 * TILE + (qi >> 3) * 32 + (qi & 3) * 8 + fh * 4;
+        if (bias && n < a.N) {
+            const uint2 b = *(const uint2*)(bias + n * 2);
+            const uint16_t* be = (const uint16_t*)&b;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                out[x][i] += E::to_f32(be[i]);
+        }
+        if (GELU) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                out[x][i] = gelu_erf(out[x][i]);
+        }
+    }
+    __syncthreads();
+    const uint32_t tile = lds_addr(smem);
+#pragma unroll
+    for (int x = 0; x < QW; ++x) {
+        const int qi = WV * x + wave;
+        const uint32_t at = tile + (uint32_t)((((qi >> 2) & 1) * 32 + fr) * OS) +
+                            (uint32_t)((qi >> 3) * 64 + (qi & 3) * 16 + fh * 8);
+        *(__attribute__((address_space(3))) uint64_t*)(uintptr_t)at =
+            pack2<DT>(out[x][0], out[x][1]) | (uint64_t)pack2<DT>(out[x][2], out[x][3]) << 32;
+    }
+    __syncthreads();
+    for (int i = tid; i < SPL_BM * RT * 4; i += 64 * WV) {
+        const int t = i / (RT * 4), c = i % (RT * 4);  // 16-byte piece c of token t
+        const int64_t m = m0 + t, n = (int64_t)j0 * TILE + c * 8;
+        if (m < a.M && n < a.N)
+            *(v4i*)(Y + (m * a.ldy + n) * 2) = lds_read16<0>(tile + t * OS + c * 16);
+    }
+}
+
 // fp32 (v_mfma_f32_16x16x4_f32: float32 products and sums, 256 FLOP per clock
 // and CU, twice the rate of unpacked VALU multiply-adds).  A wave takes 16
 // outputs (inside one block row, b_r >= 16) times 16 T tokens and walks the
@@ -1008,6 +1302,86 @@ struct Args {
     char* Y;
     bool kh;                  // sparse, 16-wide block columns: tile halves walked on their own
 };
+
+// 64-token x 1-tile-row units of a product.
+int64_t split_units(const Dims& d)
+{
+    return (d.M + SPL_BM - 1) / SPL_BM * d.n_tile_rows;
+}
+
+// Whether k_linear16_split takes a product: its units must leave k_linear16's
+// persistent workgroups short of items.  GPU time of both at 50% sparsity
+// (bf16, 32 x 32 blocks, us, split / k_linear16): K = 768: 394 tokens x 3072 7 / 20,
+// 1576 x 3072 (2400 units) 16 / 21, 3152 x 3072 (4800) 24 / 22, 6304 x 3072
+// 41 / 37; K = 384: 3152 x 1536 (2400) 12 / 13, 6304 x 1536 19 / 14.  With few
+// groups and a long reduction k_linear16 stays short of items for longer: K =
+// 3072, 768 outputs: 6304 tokens (2376 units) 31 / 67, 12608 53 / 66, 25216
+// (9456) 101 / 120, 50432 238 / 206; K = 1536, 384 outputs: 25216 tokens (4728)
+// 35 / 38, 50432 (9456) 61 / 66.  Dense, K = 3072: 6304 tokens 50 / 79, 12608
+// 90 / 81.
+constexpr int64_t SPL_UNITS = 3072, SPL_UNITS_LONG = 10240;
+bool use_split(const Dims& d, bool dense)
+{
+    // whole pairs of column tiles, at most one per lane and table half
+    if (d.K % (2 * TILE) || d.K / (2 * TILE) > SPL_MAX_PAIRS)
+        return false;
+    const bool long_k = !dense && d.n_groups <= 3 && d.K >= 1536;
+    return split_units(d) <= (long_k ? SPL_UNITS_LONG : SPL_UNITS);
+}
+
+template <bool DENSE, int RT, int WV>
+hipError_t launch_split_as(int dtype, bool gelu, const Args& a, const uint32_t* half_tiles,
+                           hipStream_t s)
+{
+    SplitDims d = {a.d.ldx, a.d.M, a.d.K, a.d.N, a.d.ldw, a.d.ldy, a.d.n_tile_rows, a.d.n_tile_cols / 2};
+    d.n_mt = (int32_t)((d.M + SPL_BM - 1) / SPL_BM);
+    d.n_rb = (d.n_tile_rows + RT - 1) / RT;
+    // whole token tiles to an XCD once every XCD gets several
+    d.xcd_tiles = d.n_mt >= 64;
+    const int64_t wgs = (int64_t)(d.xcd_tiles ? (d.n_mt + 7) / 8 * 8 : d.n_mt) * d.n_rb;
+    const dim3 grid((unsigned)wgs), block(64 * WV);
+#define LPV_SPLIT(DT_, GELU_)                                                                   \
+    hipLaunchKernelGGL((k_linear16_split<DT_, GELU_, DENSE, RT, WV>), grid, block, 0, s, d,      \
+                       a.X, a.stream, half_tiles, a.W, a.bias, a.Y)
+    if (dtype == LPV_BF16) {
+        if (gelu)
+            LPV_SPLIT(LPV_BF16, true);
+        else
+            LPV_SPLIT(LPV_BF16, false);
+    } else {
+        if (gelu)
+            LPV_SPLIT(LPV_F16, true);
+        else
+            LPV_SPLIT(LPV_F16, false);
+    }
+#undef LPV_SPLIT
+    return hipGetLastError();
+}
+
+// Rows per workgroup and waves sharing its reduction, by the units: one
+// workgroup per CU with as many waves as LDS takes while there are few, then two
+// to five smaller workgroups per CU whose start and end overlap (GPU us at K =
+// 768: 168 units 1 x 8 4.4, 2 x 8 5.4; 600 units 2 x 4 7.0, 2 x 8 9.3, 2 x 2 8.1;
+// 1200 units 2 x 2 9.5, 2 x 4 11.5; 2400 units 4 x 2 16.2, 2 x 2 18.5; K = 3072:
+// 4728 units 4 x 1 53, 4 x 2 56).
+template <bool DENSE>
+hipError_t launch_split(int dtype, bool gelu, const Args& a, const uint32_t* half_tiles, hipStream_t s)
+{
+    const int64_t u = split_units(a.d);
+    if (u <= 256)
+        return launch_split_as<DENSE, 1, 8>(dtype, gelu, a, half_tiles, s);
+    if (u <= 512)
+        return launch_split_as<DENSE, 2, 8>(dtype, gelu, a, half_tiles, s);
+    if (u <= 1024)
+        return launch_split_as<DENSE, 2, 4>(dtype, gelu, a, half_tiles, s);
+    if (u <= 2048)
+        return launch_split_as<DENSE, 2, 2>(dtype, gelu, a, half_tiles, s);
+    if constexpr (!DENSE) {
+        if (u > SPL_UNITS)
+            return launch_split_as<DENSE, 4, 1>(dtype, gelu, a, half_tiles, s);
+    }
+    return launch_split_as<DENSE, 4, 2>(dtype, gelu, a, half_tiles, s);
+}
 
 template <bool DENSE>
 hipError_t launch16(int dtype, bool gelu, Args a, hipStream_t s)
@@ -1184,6 +1558,8 @@ hipError_t launch_bsr_linear(const lpv_bsr* h, const LinearCall& c, hipStream_t 
     a.gdesc_host = h->gdesc_host;
     a.walk = h->walk;
     a.kh = h->b_c == 16;
+    if (use_split(a.d, false))
+        return launch_split<false>(h->dtype, c.gelu != 0, a, h->half_tiles, s);
     return launch16<false>(h->dtype, c.gelu != 0, a, s);
 }
 
@@ -1196,6 +1572,8 @@ hipError_t launch_dense_linear(const void* W, int64_t ldw, int64_t N, int64_t K,
     Args a = base_args(c, N, K);
     a.W = (const char*)W;
     a.d.ldw = ldw;
+    if (use_split(a.d, true))
+        return launch_split<true>(dtype, c.gelu != 0, a, nullptr, s);
     return launch16<true>(dtype, c.gelu != 0, a, s);
 }
 

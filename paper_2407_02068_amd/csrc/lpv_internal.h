@@ -42,6 +42,9 @@ struct lpv_bsr {
     int32_t* group_order;  // n_groups
     int32_t* step_ptr;     // n_groups + 1
     int32_t* group_tile0;  // n_groups + 1, first stream tile of each group
+    // half group (4 tile rows) x tile column (an even count, n_tile_cols rounded
+    // up): kept rows << 28 | first kept tile in the stream (fewer than 2^21)
+    uint32_t* half_tiles;
     int32_t* step_col;     // n_steps
     int32_t* step_bits;    // n_steps
     int32_t* step_tile;    // n_steps

@@ -220,16 +220,19 @@ __global__ __launch_bounds__(256) void k_pack_compact(PackArgs a, const int32_t*
 }
 
 // One wave per group: the group's steps in ascending tile column, with the
-// row bits and the index of the first kept tile in the operand stream.
+// row bits and the index of the first kept tile in the operand stream; and the
+// same per half group and tile column (half_tiles).
 __global__ __launch_bounds__(64) void k_sched_fill(PackArgs a, const int32_t* __restrict__ step_ptr,
                                                    const int32_t* __restrict__ group_tile0,
                                                    int32_t* __restrict__ step_col,
                                                    int32_t* __restrict__ step_bits,
-                                                   int32_t* __restrict__ step_tile)
+                                                   int32_t* __restrict__ step_tile,
+                                                   uint32_t* __restrict__ half_tiles)
 {
     const int g = blockIdx.x;
+    const int nc = (a.n_tile_cols + 1) & ~1;
     int s = step_ptr[g], t = group_tile0[g];
-    for (int tc0 = 0; tc0 < a.n_tile_cols; tc0 += 64) {
+    for (int tc0 = 0; tc0 < nc; tc0 += 64) {
         const int tc = tc0 + (int)threadIdx.x;
         const int bits = tc < a.n_tile_cols ? tile_bits(a, g, tc) : 0;
         const uint64_t b = __ballot(bits != 0);
@@ -240,6 +243,11 @@ __global__ __launch_bounds__(64) void k_sched_fill(PackArgs a, const int32_t* __
             step_col[pos] = tc;
             step_bits[pos] = bits;
             step_tile[pos] = t + inc - pc;
+        }
+        if (tc < nc) {
+            const uint32_t lo = bits & 15, hi = bits >> 4, t0 = t + inc - pc;
+            half_tiles[(int64_t)(2 * g) * nc + tc] = lo << 28 | t0;
+            half_tiles[(int64_t)(2 * g + 1) * nc + tc] = hi << 28 | (t0 + __popc(lo));
         }
         s += __popcll(b);
         t += __shfl(inc, 63, 64);
@@ -399,7 +407,7 @@ hipError_t launch_pack_fill(const PackArgs& a, const lpv_bsr* h, hipStream_t s)
         return e;
     if (a.n_groups > 0)
         hipLaunchKernelGGL(k_sched_fill, dim3(a.n_groups), dim3(64), 0, s, a, h->step_ptr,
-                           h->group_tile0, h->step_col, h->step_bits, h->step_tile);
+                           h->group_tile0, h->step_col, h->step_bits, h->step_tile, h->half_tiles);
     if (h->n_steps > 0)
         hipLaunchKernelGGL(k_stream_fill, dim3((unsigned)h->n_steps), dim3(256), 0, s, a,
                            h->step_ptr, h->step_col, h->step_bits, h->step_tile,

@@ -81,6 +81,43 @@ def test_fp32_tiles(M, N, K, b_r, b_c):
     assert_close(f64(Yd), r, "f32", "dense")
 
 
+@pytest.mark.parametrize("dense", [False, True])
+@pytest.mark.parametrize("M,N,K,b_r,b_c", [
+    (1, 16, 64, 16, 16),         # 1 row x 8 waves: one pair of columns, 16 outputs
+    (65, 112, 4160, 16, 64),     # 65 pairs (a second table half), 16 rows in the last tile
+    (577, 1280, 192, 64, 16),    # 2 x 8: 3 pairs for 8 waves
+    (640, 2528, 128, 32, 32),    # 2 x 4: an odd number of tile rows
+    (1217, 2512, 192, 16, 32),   # 2 x 2
+    (1889, 2560, 128, 64, 64),   # 4 x 2
+    (8255, 752, 1536, 16, 16),   # 4 x 1 (block-sparse; dense: the persistent kernel)
+])
+def test_reduction_split_over_waves(M, N, K, b_r, b_c, dense):
+    w = wl.custom(42, M, N, K, b_r, b_c, "f16" if N % 64 else "bf16", "bernoulli", 70,
+                  gelu=M % 2 == 1)
+    say("split", M, N, K, b_r, b_c, dense)
+    if dense:
+        Y = lpv.dense_linear(dev(w.W, w.dtype), dev(w.X, w.dtype), dev(w.bias, w.dtype),
+                             epi="gelu" if w.gelu else None)
+        r = oracle.linear(w.X, w.W, w.dtype, w.b_r, w.b_c, np.ones_like(w.mask), w.bias, gelu=w.gelu)
+    else:
+        _, Y = run_bsr(w)
+        r = ref(w)
+    assert_close(f64(Y), r, w.dtype, w.name)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("K,b_r,b_c", [(320, 32, 32), (352, 16, 16), (384, 64, 64)])
+def test_persistent_items(dtype, K, b_r, b_c):
+    # more than 3072 units of 64 tokens x 32 outputs: items of 256 x 256, ragged tokens
+    w = wl.custom(43, 64 * 64 + 33, 1536, K, b_r, b_c, dtype, "uniform", 50, gelu=True)
+    say("persistent", dtype, K, b_r, b_c)
+    _, Y = run_bsr(w)
+    assert_close(f64(Y), ref(w), dtype, w.name)
+    Yd = lpv.dense_linear(dev(w.W, dtype), dev(w.X, dtype), dev(w.bias, dtype))
+    r = oracle.linear(w.X, w.W, dtype, w.b_r, w.b_c, np.ones_like(w.mask), w.bias)
+    assert_close(f64(Yd), r, dtype, "dense")
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
 @pytest.mark.parametrize("b_r,b_c", [(16, 16), (32, 32), (64, 32)])
 def test_exact_small_integers(dtype, b_r, b_c):
