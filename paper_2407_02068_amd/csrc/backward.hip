@@ -442,8 +442,10 @@ __global__ __launch_bounds__(GW_NT, 1) void k_gradw_tiles(const GradWDims d,
         }
     }
     __syncthreads();
-    const uint64_t wmask = (uint64_t)__builtin_amdgcn_readfirstlane(s_mask[0]) |
-                           ((uint64_t)__builtin_amdgcn_readfirstlane(s_mask[1]) << 32);
+    // (readfirstlane returns a signed int: without the casts bit 31 -- row 3,
+    // column 7 -- would spread over rows 4 .. 7, existing or not)
+    const uint64_t wmask = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)s_mask[0]) |
+                           (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)s_mask[1]) << 32;
     const int n_kept = __popcll(wmask);
     if (n_kept == 0 || m_begin >= m_end)
         return;  // uniform for the whole workgroup

@@ -100,6 +100,16 @@ def test_backward_fp32_tiles(M, N, K, b_r, b_c):
     check_all(w, G, "fp32 tiles")
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("N,sparsity", [(384, 0), (384, 50), (192, 30), (512, 60)])
+def test_backward_partial_group(dtype, N, sparsity):
+    # the last group of 8 tile rows is partial (or whole) and a window's row 3
+    # keeps its column 7: rows past the weight must neither be computed nor written
+    w, G = case(1616, N, 768, 32, 32, dtype, "uniform", sparsity, cfg=98)
+    w.mask[3::8, 7::8] = 1
+    check_all(w, G, "partial group")
+
+
 def test_backward_m0():
     w, G = case(4, 256, 256, 32, 32, "bf16", cfg=95)
     h = lpv.bsr_pack(dev(w.W, "bf16"), dev(w.mask), 32, 32)
