@@ -11,7 +11,8 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblpv.so")
-SOURCES = ["api.hip", "pack.hip", "linear.hip", "mask.hip", "backward.hip", "delta.hip", "encoder.hip"]
+SOURCES = ["api.hip", "pack.hip", "linear.hip", "mask.hip", "backward.hip", "delta.hip", "encoder.hip",
+           "stationary.hip"]
 ARCH = "gfx950"
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -25,14 +26,15 @@ FLAGS = [
 # ordinary VGPRs: they branch around each tile's instructions, and at their
 # register counts accumulators in AGPRs would be copied across every branch.
 _VGPR_MFMA = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
-SOURCE_FLAGS = {"linear.hip": _VGPR_MFMA, "backward.hip": _VGPR_MFMA, "encoder.hip": _VGPR_MFMA}
+SOURCE_FLAGS = {"linear.hip": _VGPR_MFMA, "backward.hip": _VGPR_MFMA, "encoder.hip": _VGPR_MFMA,
+                "stationary.hip": _VGPR_MFMA}
 BUILD_DIR = os.path.join(HERE, "_build")
 
 
 # Kernels whose LDS ring counts every vector-memory instruction a wave issues
 # (vmcnt): a register spill to scratch would add uncounted ones, so any
 # scratch use there fails the build.
-NO_SCRATCH = ("k_linear16", "k_linear_f32", "k_gradw_f32")
+NO_SCRATCH = ("k_linear16", "k_linear_f32", "k_gradw_f32", "k_linear16_xs")
 
 
 def check_resources(remarks):

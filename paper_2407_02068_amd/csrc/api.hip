@@ -185,10 +185,13 @@ lpv_status lpv_bsr_pack(const void* W, int64_t ldw, int64_t N, int64_t K, lpv_dt
     hipStream_t s = (hipStream_t)stream;
 
     // one buffer for gdesc (16-byte entries first), half_tiles, row_ptr,
-    // group_order, step_ptr, group_tile0 and the plan
+    // group_order, step_ptr, group_tile0, row_tile0, row_mask and the plan
+    const bool rows = es == 2 && K % (2 * lpv::TILE) == 0 && h->n_tile_cols <= lpv::XS_COLS &&
+                      h->n_tile_rows <= lpv::XS_ROWS;
     const size_t n_half = (size_t)2 * h->n_groups * (size_t)((h->n_tile_cols + 1) & ~1);
     const size_t n_meta = 4 * (size_t)h->n_groups + n_half + (size_t)(h->R + 1) +
-                          3 * (size_t)(h->n_groups + 1) + 4;
+                          3 * (size_t)(h->n_groups + 1) + 4 +
+                          (rows ? 2 * (size_t)h->n_tile_rows + 1 : 0);
     void* meta = nullptr;
     hipError_t e = dmalloc(&meta, n_meta * sizeof(int32_t));
     if (e != hipSuccess) {
@@ -209,6 +212,10 @@ lpv_status lpv_bsr_pack(const void* W, int64_t ldw, int64_t N, int64_t K, lpv_dt
     h->step_ptr = h->group_order + (h->n_groups + 1);
     h->group_tile0 = h->step_ptr + (h->n_groups + 1);
     lpv::Plan* plan_d = (lpv::Plan*)(h->group_tile0 + (h->n_groups + 1));
+    if (rows) {
+        h->row_tile0 = (int32_t*)(plan_d + 1);
+        h->row_mask = (uint32_t*)(h->row_tile0 + h->n_tile_rows + 1);
+    }
 
     lpv::PackArgs a = {};
     a.W = W;
@@ -224,6 +231,8 @@ lpv_status lpv_bsr_pack(const void* W, int64_t ldw, int64_t N, int64_t K, lpv_dt
     a.n_tile_rows = h->n_tile_rows;
     a.n_tile_cols = h->n_tile_cols;
     a.n_groups = h->n_groups;
+    a.row_tile0 = h->row_tile0;
+    a.row_mask = h->row_mask;
 
     lpv::Plan plan = {};
     const bool mfma_path = dt != LPV_F32;
@@ -271,7 +280,9 @@ lpv_status lpv_bsr_pack(const void* W, int64_t ldw, int64_t N, int64_t K, lpv_dt
         if (e == hipSuccess)
             e = dmalloc((void**)&h->walk, (size_t)h->n_walk * sizeof(int2));
         if (e == hipSuccess)
-            e = dmalloc(&h->stream_vals, (size_t)h->n_tiles * lpv::TILE * lpv::TILE * es);
+            e = dmalloc(&h->stream_vals, (size_t)h->n_tiles * lpv::TILE * lpv::TILE * es * (rows ? 2 : 1));
+        if (e == hipSuccess && rows && h->n_tiles > 0)
+            h->row_vals = (char*)h->stream_vals + (size_t)h->n_tiles * lpv::TILE * lpv::TILE * es;
     }
     if (e != hipSuccess) {
         free_handle(h);

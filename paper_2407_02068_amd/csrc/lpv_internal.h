@@ -17,6 +17,10 @@ constexpr int GROUP_TILES = 8;
 // Tokens per workgroup.
 constexpr int BM = 256;
 
+// Widest and tallest weight, in tiles, of the X-stationary kernel.
+constexpr int XS_COLS = 24;
+constexpr int XS_ROWS = 128;
+
 struct Plan {  // sizes learnt on the device during pack
     int32_t nnzb, n_steps, n_tiles, n_walk;
 };
@@ -51,6 +55,12 @@ struct lpv_bsr {
     int64_t n_walk;
     int2* walk;            // n_walk: the launch slots' walks, {col | bits << 16 | last << 24, tile}
     void* stream_vals;     // n_tiles * TILE * TILE elements, operand order
+    // the same tiles by tile row, ascending columns (weights that fit XS_COLS x
+    // XS_ROWS tiles, K a multiple of 64; NULL otherwise): row r's are row_tile0[r] .. row_tile0[r + 1],
+    // bit c of row_mask[r] set for tile column c
+    void* row_vals;        // in the stream_vals allocation
+    int32_t* row_tile0;    // n_tile_rows + 1
+    uint32_t* row_mask;    // n_tile_rows
     // workspace of lpv_bsr_grad_w (per-chunk float32 partial sums of every
     // tile), allocated on the first call and kept until destroy
     mutable void* gradw_ws;
@@ -66,6 +76,8 @@ struct PackArgs {
     int32_t b_r, b_c, R, C;
     const uint8_t* mask;
     int32_t n_tile_rows, n_tile_cols, n_groups;
+    int32_t* row_tile0;  // NULL: no row-major tiles
+    uint32_t* row_mask;
 };
 
 // pack.hip
@@ -87,6 +99,10 @@ struct LinearCall {
 hipError_t launch_bsr_linear(const lpv_bsr* h, const LinearCall& c, hipStream_t s);
 hipError_t launch_dense_linear(const void* W, int64_t ldw, int64_t N, int64_t K, int dtype,
                                const LinearCall& c, hipStream_t s);
+// stationary.hip: the product of a handle with row_vals, and whether it is the
+// faster one for M tokens
+bool use_xs(const lpv_bsr* h, int64_t M, int n_cus);
+hipError_t launch_xs_linear(const lpv_bsr* h, const LinearCall& c, int n_cus, hipStream_t s);
 
 // mask.hip
 struct MaskCall {

@@ -96,6 +96,7 @@ __global__ __launch_bounds__(PLAN_THREADS) void k_pack_plan(PackArgs a, int32_t*
     __shared__ int s_walk[MAX_GROUPS];
     __shared__ int s_wave[PLAN_WAVES];
     __shared__ int s_carry;
+    __shared__ uint32_t s_rowm[XS_ROWS + GROUP_TILES];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
     // kept blocks per block-row: one wave per row, a ballot per 64 columns
@@ -117,6 +118,13 @@ __global__ __launch_bounds__(PLAN_THREADS) void k_pack_plan(PackArgs a, int32_t*
             const int bits = tc < a.n_tile_cols ? tile_bits(a, g, tc) : 0;
             ns += __popcll(__ballot(bits != 0));
             nt += wave_sum(__popc(bits));
+            if (a.row_mask)  // (one pass: at most 24 tile columns)
+#pragma unroll
+                for (int j = 0; j < GROUP_TILES; ++j) {
+                    const uint64_t m = __ballot((bits >> j) & 1);
+                    if (lane == 0)
+                        s_rowm[g * GROUP_TILES + j] = (uint32_t)m;
+                }
         }
         if (lane == 0) {
             s_gsteps[g] = ns;
@@ -131,6 +139,21 @@ __global__ __launch_bounds__(PLAN_THREADS) void k_pack_plan(PackArgs a, int32_t*
     const int n_tiles = block_exclusive_scan(s_gtiles, a.n_groups, s_wave, &s_carry);
     for (int r = tid; r < a.R; r += PLAN_THREADS)
         row_ptr[r] = s_cnt[r];
+    if (a.row_mask && wave == 0) {
+        int at = 0;
+        for (int r0 = 0; r0 < a.n_tile_rows; r0 += 64) {
+            const int r = r0 + lane;
+            const uint32_t m = r < a.n_tile_rows ? s_rowm[r] : 0;
+            const int inc = wave_inclusive_scan(__popc(m));
+            if (r < a.n_tile_rows) {
+                a.row_mask[r] = m;
+                a.row_tile0[r] = at + inc - __popc(m);
+            }
+            at += __shfl(inc, 63, 64);
+        }
+        if (lane == 0)
+            a.row_tile0[a.n_tile_rows] = at;
+    }
     for (int g = tid; g < a.n_groups; g += PLAN_THREADS) {
         step_ptr[g] = s_gsteps[g];
         group_tile0[g] = s_gtiles[g];
@@ -258,12 +281,14 @@ __global__ __launch_bounds__(64) void k_sched_fill(PackArgs a, const int32_t* __
 // Within a tile, 16-byte chunk (ks, l) holds W[row0 + (l & 31)][col0 + 16 ks +
 // 8 (l >> 5) .. + 8]: lane l's operand of the ks-th 32x32x16 instruction.
 // Elements of dropped blocks inside a kept tile are zero (selected, never
-// copied), as are rows / columns past the weight's edge.
+// copied), as are rows / columns past the weight's edge.  row_vals, if any, gets
+// the same tiles by tile row.
 __global__ __launch_bounds__(256) void k_stream_fill(PackArgs a, const int32_t* __restrict__ step_ptr,
                                                      const int32_t* __restrict__ step_col,
                                                      const int32_t* __restrict__ step_bits,
                                                      const int32_t* __restrict__ step_tile,
-                                                     uint4* __restrict__ stream)
+                                                     uint4* __restrict__ stream,
+                                                     uint4* __restrict__ row_vals)
 {
     const int st = blockIdx.x;
     // group of this step: the last g with step_ptr[g] <= st
@@ -292,6 +317,10 @@ __global__ __launch_bounds__(256) void k_stream_fill(PackArgs a, const int32_t* 
         if (n < a.N && k < a.K && a.mask[(n / a.b_r) * a.C + k / a.b_c] != 0)
             v = *(const uint4*)((const char*)a.W + (n * a.ldw + k) * a.es);
         stream[(int64_t)(tile0 + jj) * 128 + rem] = v;
+        if (row_vals) {
+            const int r = g * GROUP_TILES + j;
+            row_vals[(int64_t)(a.row_tile0[r] + __popc(a.row_mask[r] & ((1u << col) - 1))) * 128 + rem] = v;
+        }
     }
 }
 
@@ -411,7 +440,7 @@ hipError_t launch_pack_fill(const PackArgs& a, const lpv_bsr* h, hipStream_t s)
     if (h->n_steps > 0)
         hipLaunchKernelGGL(k_stream_fill, dim3((unsigned)h->n_steps), dim3(256), 0, s, a,
                            h->step_ptr, h->step_col, h->step_bits, h->step_tile,
-                           (uint4*)h->stream_vals);
+                           (uint4*)h->stream_vals, (uint4*)h->row_vals);
     if (a.n_groups > 0)
         hipLaunchKernelGGL(k_walk_fill, dim3(a.n_groups), dim3(64), 0, s, a, h->gdesc, h->step_ptr,
                            h->step_col, h->step_bits, h->step_tile, h->walk);

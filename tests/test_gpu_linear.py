@@ -108,14 +108,46 @@ def test_reduction_split_over_waves(M, N, K, b_r, b_c, dense):
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("K,b_r,b_c", [(320, 32, 32), (352, 16, 16), (384, 64, 64)])
 def test_persistent_items(dtype, K, b_r, b_c):
-    # more than 3072 units of 64 tokens x 32 outputs: items of 256 x 256, ragged tokens
-    w = wl.custom(43, 64 * 64 + 33, 1536, K, b_r, b_c, dtype, "uniform", 50, gelu=True)
+    # more than 3072 units of 64 tokens x 32 outputs, too dense for (or not a multiple of 64
+    # columns as) the kernel with X in registers: items of 256 x 256, ragged tokens
+    w = wl.custom(43, 64 * 64 + 33, 1536, K, b_r, b_c, dtype, "uniform", 20, gelu=True)
     say("persistent", dtype, K, b_r, b_c)
     _, Y = run_bsr(w)
     assert_close(f64(Y), ref(w), dtype, w.name)
     Yd = lpv.dense_linear(dev(w.W, dtype), dev(w.X, dtype), dev(w.bias, dtype))
     r = oracle.linear(w.X, w.W, dtype, w.b_r, w.b_c, np.ones_like(w.mask), w.bias)
     assert_close(f64(Yd), r, dtype, "dense")
+
+
+@pytest.mark.parametrize("M,N,K,b_r,b_c,kind,sparsity", [
+    (42 * 256 + 1, 1552, 64, 16, 32, "uniform", 60),     # one pair, 49 rows (the last of 16 outputs)
+    (16 * 256 - 31, 4096, 384, 32, 32, "zipf", 70),      # 12 columns, the most rows, skewed
+    (22 * 256 + 33, 3072, 448, 64, 64, "bernoulli", 50), # 14 columns in the 24-column kernel
+    (86 * 256 + 200, 768, 768, 32, 32, "uniform", 98),   # rows with no tile
+    (22 * 256, 3072, 768, 16, 16, "uniform", 90),        # 16-wide columns
+    (86 * 256, 768, 192, 32, 32, "none", 100),           # nothing kept: the bias
+])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_x_in_registers(M, N, K, b_r, b_c, kind, sparsity, dtype):
+    # at least 2048 rows of 256 tokens, at most 70% of the tiles kept (50% with 16-wide columns)
+    w = wl.custom(44, M, N, K, b_r, b_c, dtype, kind, sparsity, gelu=M % 2 == 1)
+    say("X in registers", M, N, K, b_r, b_c, kind, dtype)
+    _, Y = run_bsr(w)
+    rows = np.unique(np.r_[0:40, 200:300, M // 2:M // 2 + 70, M - 300:M])  # (every row is too much oracle)
+    assert_close(f64(Y)[rows], ref(w, w.X[rows]), dtype, w.name)
+    # every row, against the same rows through the kernel for few token tiles.  The
+    # float32 sums differ in their last bits only, so the results are at most
+    # neighbours: with p significant bits (8, 11) those are 2^(1 - p) of the value
+    # apart, plus the sums' own error (1e-5) where the value nearly cancels
+    h = lpv.bsr_pack(dev(w.W, dtype), dev(w.mask), b_r, b_c)
+    part = Y.new_empty(Y.shape)
+    X, b = dev(w.X, dtype), dev(w.bias, dtype)
+    for i in range(0, M, 512):
+        lpv.bsr_linear(h, X[i:i + 512], b, part[i:i + 512], epi="gelu" if w.gelu else None)
+    torch.cuda.synchronize()
+    d = (Y.float() - part.float()).abs()
+    ulp = 2.0 ** -7 if dtype == "bf16" else 2.0 ** -10
+    assert (d <= 1.01 * ulp * torch.maximum(Y.float().abs(), part.float().abs()) + 1e-5).all()
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
