@@ -13,70 +13,40 @@
 // (per-sample gradients, grad, and W itself for |d|^2) with -W over every
 // block: one pass over the per-sample gradients, which bounds the time (HBM).
 //
-//   k_rank         rank of each block by (-score, index) and its inverse
-//   k_delta_dots   float64 block dot products, one workgroup per (block-row,
-//                  vector)
+//   k_delta_dots   the block scores, and the float64 block dot products, one workgroup
+//                  per (block-row, 4 vectors)
+//   k_rank         (mask.hip) the blocks in the order of (-score, index)
 //   k_delta_steps  each vector's sum over each ratio step's blocks
 //   k_delta_finish one workgroup: the update, step by step
 // All sums run in a fixed order (float64), so results do not depend on timing.
 #include "lpv_device.h"
 #include "lpv_internal.h"
+#include "lpv_scores.h"
 
 namespace lpv {
 namespace {
 
-// rank[b] = #{b' : score(b') > score(b), or equal and b' < b}; perm[rank[b]] = b.
-// Scores are non-negative, so their bit patterns order like their values.
-// Workgroup: 64 blocks (lane l: block 64 x + l) times RANK_WAVES waves; wave w
-// counts the keys ahead of its lane's block in the w-th part of the key range
-// (each key read once per wave, a wave-uniform load); the parts' integer
-// counts are added in LDS (exact in any order) and the permutation written.
-constexpr int RANK_WAVES = 16;
-
-__global__ __launch_bounds__(64 * RANK_WAVES) void k_rank(const double* __restrict__ scores,
-                                                          int64_t nb, int32_t* __restrict__ perm)
+// 8 consecutive elements as loaded (16-byte aligned), and element j of them in
+// float64.
+template <int DT> struct Raw8 {
+    uint4 v[DT == LPV_F32 ? 2 : 1];
+};
+template <int DT> __device__ inline Raw8<DT> load8(const char* base, int64_t idx)
 {
-    __shared__ int32_t s_cnt[RANK_WAVES][64];
-    const int lane = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int64_t b = (int64_t)blockIdx.x * 64 + lane;
-    const uint64_t* keys = (const uint64_t*)scores;
-    const uint64_t key = keys[min(b, nb - 1)];
-    const int64_t per = (nb + RANK_WAVES - 1) / RANK_WAVES;
-    const int64_t k0 = min(nb, (int64_t)w * per), k1 = min(nb, k0 + per);
-    int32_t r = 0;
-#pragma unroll 8
-    for (int64_t i = k0; i < k1; ++i) {
-        const uint64_t k2 = keys[i];
-        r += (k2 > key) || (k2 == key && i < b);
-    }
-    s_cnt[w][lane] = r;
-    __syncthreads();
-    if (w == 0 && b < nb) {
-        int32_t rank = 0;
-#pragma unroll
-        for (int j = 0; j < RANK_WAVES; ++j)
-            rank += s_cnt[j][lane];
-        perm[rank] = (int32_t)b;
-    }
+    Raw8<DT> r;
+    r.v[0] = *(const uint4*)(base + idx * (DT == LPV_F32 ? 4 : 2));
+    if constexpr (DT == LPV_F32)
+        r.v[1] = *(const uint4*)(base + idx * 4 + 16);
+    return r;
 }
-
-// The 8 elements at idx .. idx + 7 (idx a multiple of 8, 16-byte aligned) in
-// float64, from 16-byte loads.
-template <int DT> __device__ inline void load8(const char* base, int64_t idx, double* out)
+template <int DT> __device__ inline double elem(const Raw8<DT>& r, int j)
 {
     if constexpr (DT == LPV_F32) {
-        const float4 a = *(const float4*)(base + idx * 4), b = *(const float4*)(base + idx * 4 + 16);
-        out[0] = a.x, out[1] = a.y, out[2] = a.z, out[3] = a.w;
-        out[4] = b.x, out[5] = b.y, out[6] = b.z, out[7] = b.w;
+        const uint32_t w[4] = {r.v[j >> 2].x, r.v[j >> 2].y, r.v[j >> 2].z, r.v[j >> 2].w};
+        return (double)__uint_as_float(w[j & 3]);
     } else {
-        const uint4 u = *(const uint4*)(base + idx * 2);
-        const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            out[2 * i] = (double)Elem<DT>::to_f32((uint16_t)(w[i] & 0xffffu));
-            out[2 * i + 1] = (double)Elem<DT>::to_f32((uint16_t)(w[i] >> 16));
-        }
+        const uint32_t w[4] = {r.v[0].x, r.v[0].y, r.v[0].z, r.v[0].w};
+        return (double)Elem<DT>::to_f32((uint16_t)(w[j >> 1] >> (16 * (j & 1))));
     }
 }
 
@@ -88,14 +58,29 @@ template <int DT> __device__ inline void load8(const char* base, int64_t idx, do
 // into G = 256 / nch interleaved groups as well.  Thread (g, q) sums chunk q
 // over rows g, g + G, ... (ascending); a block's sum then adds its chunks' sums
 // group by group, in column order.
+//
+// The first score_wgs workgroups take the blocks' Taylor scores instead
+// (wg_block_scores, score_nb blocks each): their serial additions then run beside
+// the dot products' loads, which bound the launch (a launch of its own took 13 us).
+constexpr int DELTA_SC_LDS = 8192;  // bytes of score terms per workgroup
+
 template <int DT, int VPW>
-__global__ __launch_bounds__(256) void k_delta_dots(const DeltaCall c, int32_t C,
+__global__ __launch_bounds__(256) void k_delta_dots(const DeltaCall c, int32_t R, int32_t C,
+                                                    int32_t score_wgs, int32_t score_nb,
+                                                    double* __restrict__ scores,
                                                     double* __restrict__ dots)
 {
-    extern __shared__ double s_part[];  // VPW x G x nch chunk sums
+    extern __shared__ double2 s_dyn[];
+    double* s_part = (double*)s_dyn;  // VPW x G x nch chunk sums
     constexpr int ES = DT == LPV_F32 ? 4 : 2;
-    const int r = blockIdx.x;
-    const int64_t nv = c.n_samples + 2, v0 = (int64_t)blockIdx.y * VPW;
+    if ((int)blockIdx.x < score_wgs) {
+        wg_block_scores<DT, true, 256>((const char*)c.W, c.ldw, (const char*)c.grad, c.ldg, C, c.b_r,
+                                       c.b_c, score_nb, blockIdx.x, s_dyn, scores);
+        return;
+    }
+    const int64_t wg = (int64_t)blockIdx.x - score_wgs;
+    const int r = (int)(wg % R);
+    const int64_t nv = c.n_samples + 2, v0 = wg / R * VPW;
     const int nvv = (int)min((int64_t)VPW, nv - v0);
     const char* xs[VPW];
     int64_t lx[VPW];
@@ -122,20 +107,34 @@ __global__ __launch_bounds__(256) void k_delta_dots(const DeltaCall c, int32_t C
 #pragma unroll
         for (int u = 0; u < VPW; ++u)
             acc[u] = 0.0;
-#pragma unroll 2
-        for (int i = g; i < c.b_r; i += G) {
-            const int64_t row = (int64_t)r * c.b_r + i;
-            double wv[8];
-            load8<DT>(w, row * c.ldw + (int64_t)q * 8, wv);
+        // RB rows of the W chunk and of the vectors' chunks in flight at a time (the
+        // scheduling barrier keeps the loads together: they are what hides HBM)
+        constexpr int RB = DT == LPV_F32 ? 2 : 4;
+        for (int i = g; i < c.b_r; i += RB * G) {
+            Raw8<DT> wr[RB], xr[RB][VPW];
 #pragma unroll
-            for (int u = 0; u < VPW; ++u) {
-                if (u < nvv) {
-                    double xv[8];
-                    load8<DT>(xs[u], row * lx[u] + (int64_t)q * 8, xv);
+            for (int b = 0; b < RB; ++b) {
+                // (rows past the block repeat its last and are not added)
+                const int64_t row = (int64_t)r * c.b_r + min(i + b * G, c.b_r - 1);
+                wr[b] = load8<DT>(w, row * c.ldw + (int64_t)q * 8);
+#pragma unroll
+                for (int u = 0; u < VPW; ++u)
+                    xr[b][u] = load8<DT>(xs[u], row * lx[u] + (int64_t)q * 8);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int b = 0; b < RB; ++b) {
+                if (i + b * G >= c.b_r)
+                    break;
+                double wv[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    wv[j] = -elem<DT>(wr[b], j);
+#pragma unroll
+                for (int u = 0; u < VPW; ++u)
 #pragma unroll
                     for (int j = 0; j < 8; ++j)
-                        acc[u] += xv[j] * -wv[j];
-                }
+                        acc[u] += elem<DT>(xr[b][u], j) * wv[j];
             }
         }
 #pragma unroll
@@ -269,26 +268,27 @@ hipError_t launch_delta_curve(const DeltaCall& c, hipStream_t s)
     double* q = dots + nv * nb;
     double* term = q + (int64_t)c.n_points * nv;
     int32_t* perm = (int32_t*)(term + c.n_points);
-    MaskCall m = {c.W, c.ldw, c.grad, c.ldg, c.N, c.K, c.dtype, c.b_r, c.b_c, 0, nullptr, scores};
-    e = launch_block_scores(m, s);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_rank, dim3((unsigned)((nb + 63) / 64)), dim3(64 * RANK_WAVES), 0, s,
-                           (const double*)scores, nb, perm);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess) {
+    {
         const int64_t nch = c.K / 8;
         const int64_t part = (nch >= 256 ? nch : 256 / nch * nch) * (int64_t)sizeof(double);
         // vectors per workgroup: 4 while their chunk sums fit 64 KB of LDS
         const int vpw = part * 4 <= 65536 ? 4 : 1;
-        const dim3 grid((unsigned)R, (unsigned)((nv + vpw - 1) / vpw));
-        const size_t lds = (size_t)(part * vpw);
-#define LPV_DOTS(DT_)                                                                         \
-    do {                                                                                      \
-        if (vpw == 4)                                                                         \
-            hipLaunchKernelGGL((k_delta_dots<DT_, 4>), grid, dim3(256), lds, s, c, C, dots); \
-        else                                                                                  \
-            hipLaunchKernelGGL((k_delta_dots<DT_, 1>), grid, dim3(256), lds, s, c, C, dots); \
+        // blocks per score workgroup: as many as fit (at least one, of at most 32 KB)
+        const int bytes = c.b_r * c.b_c * 8;
+        const int snb = min(max(1, DELTA_SC_LDS / bytes), C);
+        const int64_t score_wgs = (int64_t)R * ((C + snb - 1) / snb);
+        const int64_t dot_wgs = (int64_t)R * ((nv + vpw - 1) / vpw);
+        const dim3 grid((unsigned)(score_wgs + dot_wgs));
+        const int64_t s_lds = (int64_t)snb * (bytes + 16), d_lds = part * vpw;
+        const size_t lds = (size_t)(s_lds > d_lds ? s_lds : d_lds);
+#define LPV_DOTS(DT_)                                                                            \
+    do {                                                                                         \
+        if (vpw == 4)                                                                            \
+            hipLaunchKernelGGL((k_delta_dots<DT_, 4>), grid, dim3(256), lds, s, c, R, C,         \
+                               (int32_t)score_wgs, snb, scores, dots);                           \
+        else                                                                                     \
+            hipLaunchKernelGGL((k_delta_dots<DT_, 1>), grid, dim3(256), lds, s, c, R, C,         \
+                               (int32_t)score_wgs, snb, scores, dots);                           \
     } while (0)
         if (c.dtype == LPV_BF16)
             LPV_DOTS(LPV_BF16);
@@ -299,6 +299,8 @@ hipError_t launch_delta_curve(const DeltaCall& c, hipStream_t s)
 #undef LPV_DOTS
         e = hipGetLastError();
     }
+    if (e == hipSuccess)
+        e = launch_rank(scores, nb, 0, perm, nullptr, s);
     if (e == hipSuccess) {
         const int64_t waves = nv * c.n_points;
         hipLaunchKernelGGL(k_delta_steps, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, c, nb,

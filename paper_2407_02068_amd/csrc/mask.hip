@@ -17,6 +17,7 @@
 // like their values; the selection works on those 64-bit keys.
 #include "lpv_device.h"
 #include "lpv_internal.h"
+#include "lpv_scores.h"
 
 namespace lpv {
 namespace {
@@ -29,30 +30,6 @@ template <int DT> __device__ inline double load_f64(const char* base, int64_t id
     if (DT == LPV_BF16)
         return (double)__uint_as_float((uint32_t)bits << 16);
     return (double)(float)__builtin_bit_cast(_Float16, bits);
-}
-
-// 8 consecutive elements (16-byte aligned) decoded to float64, from 16-byte loads.
-template <int DT> __device__ inline void load8_f64(const char* base, int64_t idx, double* out)
-{
-    if (DT == LPV_F32) {
-        const float4 a = *(const float4*)(base + idx * 4), b = *(const float4*)(base + idx * 4 + 16);
-        out[0] = a.x, out[1] = a.y, out[2] = a.z, out[3] = a.w;
-        out[4] = b.x, out[5] = b.y, out[6] = b.z, out[7] = b.w;
-    } else {
-        const uint4 u = *(const uint4*)(base + idx * 2);
-        const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint16_t lo = (uint16_t)(w[j] & 0xffffu), hi = (uint16_t)(w[j] >> 16);
-            if (DT == LPV_BF16) {
-                out[2 * j] = (double)__uint_as_float((uint32_t)lo << 16);
-                out[2 * j + 1] = (double)__uint_as_float((uint32_t)hi << 16);
-            } else {
-                out[2 * j] = (double)(float)__builtin_bit_cast(_Float16, lo);
-                out[2 * j + 1] = (double)(float)__builtin_bit_cast(_Float16, hi);
-            }
-        }
-    }
 }
 
 // One thread per block (r, c) = blockIdx.x * 256 + threadIdx.x (row-major).
@@ -106,13 +83,8 @@ __global__ __launch_bounds__(256) void k_block_scores(const char* __restrict__ W
     scores[i] = TAYLOR ? s / (double)(b_r * b_c) : s;
 }
 
-// The same scores with the loads taken off the additions' path: a workgroup
-// takes NB consecutive blocks of one block row; all its threads load them
-// with 16-byte reads and write every element's term (|w g| or w w, exact in
-// float64) to LDS; then thread j adds up block j's terms from LDS, one after
-// the other in the same row-major order (the same value bit for bit).  A
-// block's terms sit at a stride of its size plus 16 bytes, so the adding
-// threads' 16-byte reads fall in distinct banks.
+// The same scores through LDS (wg_block_scores): as many blocks of one block row per
+// workgroup as fit SC_LDS bytes of float64 terms.
 constexpr int SC_THREADS = 256;
 constexpr int SC_LDS = 131072;  // bytes of float64 terms per workgroup
 
@@ -125,57 +97,95 @@ __global__ __launch_bounds__(SC_THREADS) void k_block_scores_lds(const char* __r
                                                                  int32_t nb,
                                                                  double* __restrict__ scores)
 {
-#pragma clang fp contract(off)
     // at most SC_LDS bytes of terms and 16 bytes of padding per block
     // (blocks of at least 256 elements: at most SC_LDS / 2048 blocks)
     __shared__ double2 terms[(SC_LDS + 16 * (SC_LDS / 2048)) / 16];
-    const int64_t n_chunks = (C + nb - 1) / nb;
-    const int64_t r = blockIdx.x / n_chunks, c0 = (blockIdx.x - r * n_chunks) * nb;
-    const int nbk = (int)min((int64_t)nb, C - c0);  // blocks of this workgroup
-    const int n_el = b_r * b_c;
-    const int stride = n_el / 2 + 1;                  // double2 units per block
-    const int u_row = b_c / 8;                        // 8-element units per block row
-    const int units = nbk * b_r * u_row;
-    for (int i = threadIdx.x; i < units; i += SC_THREADS) {
-        const int q = i % u_row, t = i / u_row, j = t % nbk, a = t / nbk;
-        const int64_t n = r * b_r + a, k = (c0 + j) * b_c + 8 * q;
-        double w[8], g[8];
-        load8_f64<DT>(W, n * ldw + k, w);
-        if (TAYLOR)
-            load8_f64<DT>(G, n * ldg + k, g);
-        double2* dst = terms + j * stride + (a * b_c + 8 * q) / 2;
+    wg_block_scores<DT, TAYLOR, SC_THREADS>(W, ldw, G, ldg, C, b_r, b_c, nb, blockIdx.x, terms, scores);
+}
+
+// rank[b] = #{b' : score(b') > score(b), or equal and b' < b}: perm[rank[b]] = b
+// (perm, if given) and mask[b] = rank[b] < n_keep (mask, if given).  Scores are
+// non-negative, so their bit patterns order like their values.  Workgroup: RANK_B
+// blocks; thread t counts for block t % RANK_B the keys t / RANK_B, t / RANK_B +
+// RANK_PARTS, ... above it, and at or above it; only where another key is equal
+// does a second pass count the equal ones before it.  The keys come through LDS
+// (RANK_CHUNK at a time); integer counts, exact in any order.  Bound: the 64-bit
+// compares, so few blocks per workgroup and the whole chip (64 blocks per workgroup
+// kept 36 CUs busy with 2304 blocks: 12.6 us; this 5.4).
+constexpr int RANK_B = 8;
+constexpr int RANK_NT = 1024;
+constexpr int RANK_PARTS = RANK_NT / RANK_B;
+constexpr int RANK_CHUNK = 4096;  // 32 KB of keys
+// Most blocks for which the selection ranks every block (quadratic work).
+constexpr int64_t RANK_MAX = 8192;
+
+__global__ __launch_bounds__(RANK_NT) void k_rank(const double* __restrict__ scores, int64_t nb,
+                                                  int64_t n_keep, int32_t* __restrict__ perm,
+                                                  uint8_t* __restrict__ mask)
+{
+    __shared__ uint64_t s_keys[RANK_CHUNK];
+    __shared__ int32_t s_cnt[RANK_NT / 64][RANK_B];
+    __shared__ int s_tie;
+    const int tid = threadIdx.x, part = tid / RANK_B;
+    const int64_t b = (int64_t)blockIdx.x * RANK_B + tid % RANK_B;
+    const uint64_t* keys = (const uint64_t*)scores;
+    const uint64_t key = keys[min(b, nb - 1)];
+    if (tid == 0)
+        s_tie = 0;
+    // the threads' counts of a block, added over the workgroup (for tid < RANK_B)
+    auto add_up = [&](int32_t v) {
 #pragma unroll
-        for (int e = 0; e < 8; e += 2) {
-            double t0, t1;
-            if (TAYLOR) {
-                const double p0 = w[e] * g[e], p1 = w[e + 1] * g[e + 1];
-                t0 = p0 < 0.0 ? -p0 : p0;
-                t1 = p1 < 0.0 ? -p1 : p1;
-            } else {
-                t0 = w[e] * w[e];
-                t1 = w[e + 1] * w[e + 1];
-            }
-            dst[e / 2] = double2{t0, t1};
+        for (int o = RANK_B; o < 64; o <<= 1)
+            v += __shfl_xor(v, o, 64);
+        __syncthreads();
+        if ((tid & 63) < RANK_B)
+            s_cnt[tid >> 6][tid & 63] = v;
+        __syncthreads();
+        int32_t sum = 0;
+        if (tid < RANK_B)
+#pragma unroll
+            for (int j = 0; j < RANK_NT / 64; ++j)
+                sum += s_cnt[j][tid];
+        return sum;
+    };
+    auto stage = [&](int64_t c0) {  // keys c0 .. into LDS; how many
+        const int n = (int)min((int64_t)RANK_CHUNK, nb - c0);
+        __syncthreads();  // the chunk before is counted
+        for (int i = tid; i < n; i += RANK_NT)
+            s_keys[i] = keys[c0 + i];
+        __syncthreads();
+        return n;
+    };
+    int32_t above = 0, least = 0;
+    for (int64_t c0 = 0; c0 < nb; c0 += RANK_CHUNK) {
+        const int n = stage(c0);
+#pragma unroll 4
+        for (int i = part; i < n; i += RANK_PARTS) {
+            const uint64_t k2 = s_keys[i];
+            above += k2 > key;
+            least += k2 >= key;
         }
     }
+    int32_t rank = add_up(above);
+    const int32_t equal = add_up(least) - rank;  // the block itself and its ties
+    if (tid < RANK_B && b < nb && equal > 1)
+        s_tie = 1;
     __syncthreads();
-    const int j = threadIdx.x;
-    if (j >= nbk)
-        return;
-    const double2* src = terms + j * stride;
-    double s = 0.0;
-    for (int e = 0; e < n_el / 2; e += 4) {  // n_el is a multiple of 8
-        const double2 v0 = src[e], v1 = src[e + 1], v2 = src[e + 2], v3 = src[e + 3];
-        s = s + v0.x;
-        s = s + v0.y;
-        s = s + v1.x;
-        s = s + v1.y;
-        s = s + v2.x;
-        s = s + v2.y;
-        s = s + v3.x;
-        s = s + v3.y;
+    if (s_tie) {  // (uniform)
+        int32_t before = 0;
+        for (int64_t c0 = 0; c0 < nb; c0 += RANK_CHUNK) {
+            const int n = stage(c0);
+            for (int i = part; i < n; i += RANK_PARTS)
+                before += s_keys[i] == key && c0 + i < b;
+        }
+        rank += add_up(before);
     }
-    scores[r * C + c0 + j] = TAYLOR ? s / (double)n_el : s;
+    if (tid < RANK_B && b < nb) {
+        if (perm)
+            perm[rank] = (int32_t)b;
+        if (mask)
+            mask[b] = rank < n_keep;
+    }
 }
 
 constexpr int SEL_THREADS = 1024;
@@ -363,12 +373,24 @@ hipError_t launch_block_scores(const MaskCall& m, hipStream_t s)
     return hipGetLastError();
 }
 
+hipError_t launch_rank(const double* scores, int64_t nb, int64_t n_keep, int32_t* perm,
+                       uint8_t* mask, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_rank, dim3((unsigned)((nb + RANK_B - 1) / RANK_B)), dim3(RANK_NT), 0, s, scores,
+                       nb, n_keep, perm, mask);
+    return hipGetLastError();
+}
+
 hipError_t launch_mask_topk(const MaskCall& m, hipStream_t s)
 {
     const int64_t nb = (m.N / m.b_r) * (m.K / m.b_c);
     const hipError_t e = launch_block_scores(m, s);
     if (e != hipSuccess)
         return e;
+    // counting ahead of every block over the whole chip against eight dependent
+    // passes of one workgroup: 2304 blocks 5.4 us, 16.1; 8192 equal
+    if (nb <= RANK_MAX)
+        return launch_rank(m.scores, nb, m.n_keep, nullptr, m.mask, s);
     hipLaunchKernelGGL(k_mask_topk, dim3(1), dim3(SEL_THREADS), 0, s, (const double*)m.scores, nb,
                        m.n_keep, m.mask);
     return hipGetLastError();
