@@ -228,8 +228,8 @@ lpv_status lpv_mask_topk(const void* W, int64_t ldw, int64_t N, int64_t K, lpv_d
  *   lpv_bsr_linear(ht, G, ldg, M, NULL, dX, lddx, LPV_EPI_NONE, stream)
  * computes dX = G W~ (M x K).  Its BSR arrays are those lpv_bsr_pack gives for
  * the transposed weight and mask.  Device work on `stream`, synchronised
- * before returning (like lpv_bsr_pack); temporary device memory of K N
- * elements is allocated and freed.  *out receives the handle (release it with
+ * before returning (like lpv_bsr_pack); temporary device memory of 5
+ * bytes per block is allocated and freed.  *out receives the handle (release it with
  * lpv_bsr_destroy), NULL on failure.
  * Errors: INVALID_ARG, SHAPE (K N too large for pack), ALLOC, HIP.
  */

@@ -111,13 +111,156 @@ void free_handle(lpv_bsr* h)
 {
     if (!h)
         return;
-    void* bufs[] = {h->meta, h->col_idx, h->values, h->step_col, h->step_bits, h->step_tile,
-                    h->walk, h->stream_vals, h->gradw_ws};
+    void* bufs[] = {h->meta, h->data, h->gradw_ws};
     for (void* p : bufs)
         if (p)
             (void)hipFree(p);
     delete[] h->gdesc_host;
     delete h;
+}
+
+// lpv_bsr_pack after its checks: `a` brings the source and the mask.
+lpv_status pack_weight(lpv::PackArgs a, int64_t N, int64_t K, int dt, int32_t b_r, int32_t b_c,
+                       hipStream_t s, lpv_bsr** out)
+{
+    const int es = elem_size(dt);
+    const bool mfma_path = dt != LPV_F32;
+    lpv_bsr* h = new (std::nothrow) lpv_bsr();
+    if (!h)
+        return fail(LPV_ERR_ALLOC, "host allocation failed");
+    h->N = N;
+    h->K = K;
+    h->b_r = b_r;
+    h->b_c = b_c;
+    h->R = (int32_t)(N / b_r);
+    h->C = (int32_t)(K / b_c);
+    h->dtype = dt;
+    h->n_tile_rows = (int32_t)((N + lpv::TILE - 1) / lpv::TILE);
+    h->n_tile_cols = (int32_t)((K + lpv::TILE - 1) / lpv::TILE);
+    h->n_groups = (h->n_tile_rows + lpv::GROUP_TILES - 1) / lpv::GROUP_TILES;
+
+    // The first buffer, int32 words: gdesc (16-byte entries) and the plan after it (one
+    // copy to the host brings both), walk (8-byte entries), half_tiles, row_ptr,
+    // group_order, step_ptr, group_tile0, row_tile0, row_mask and the steps.  The step
+    // and walk arrays are sized for every column of every group.  (Buffers under about
+    // 2 MB are cut from memory the runtime holds, 1 us; a larger one costs tens to hundreds
+    // of us to map and to free, so a handle has one of each.)
+    const bool rows = mfma_path && K % (2 * lpv::TILE) == 0 && h->n_tile_cols <= lpv::XS_COLS &&
+                      h->n_tile_rows <= lpv::XS_ROWS;
+    const size_t ng = (size_t)h->n_groups, nc = (size_t)((h->n_tile_cols + 1) & ~1);
+    const size_t n_step = mfma_path ? ng * nc : 0;
+    const size_t n_walk = mfma_path ? ng * (nc > 2 ? nc : 2) : 0;
+    const size_t n_half = 2 * n_step;
+    const size_t n_meta = 4 * ng + 4 + 2 * n_walk + n_half + (size_t)(h->R + 1) + 3 * (ng + 1) +
+                          (rows ? 2 * (size_t)h->n_tile_rows + 1 : 0) + 3 * n_step;
+    hipError_t e = dmalloc(&h->meta, n_meta * sizeof(int32_t));
+    if (e != hipSuccess) {
+        free_handle(h);
+        return e == hipErrorOutOfMemory ? fail(LPV_ERR_ALLOC, "device allocation failed")
+                                        : hip_fail(e, "hipMalloc");
+    }
+    e = hipGetDevice(&h->device);
+    if (e != hipSuccess) {
+        free_handle(h);
+        return hip_fail(e, "hipGetDevice");
+    }
+    static_assert(sizeof(lpv::Plan) == sizeof(int4), "the plan takes one entry after gdesc");
+    h->gdesc = (int4*)h->meta;
+    lpv::Plan* plan_d = (lpv::Plan*)(h->gdesc + ng);
+    int32_t* at = (int32_t*)(plan_d + 1);
+    auto take = [&at](size_t n) {
+        int32_t* p = at;
+        at += n;
+        return p;
+    };
+    if (mfma_path) {
+        h->walk = (int2*)take(2 * n_walk);
+        h->half_tiles = (uint32_t*)take(n_half);
+    }
+    h->row_ptr = take((size_t)h->R + 1);
+    h->group_order = take(ng + 1);
+    h->step_ptr = take(ng + 1);
+    h->group_tile0 = take(ng + 1);
+    if (rows) {
+        h->row_tile0 = take((size_t)h->n_tile_rows + 1);
+        h->row_mask = (uint32_t*)take((size_t)h->n_tile_rows);
+    }
+    if (mfma_path) {
+        h->step_col = take(n_step);
+        h->step_bits = take(n_step);
+        h->step_tile = take(n_step);
+    }
+
+    a.N = N;
+    a.K = K;
+    a.es = es;
+    a.b_r = b_r;
+    a.b_c = b_c;
+    a.lr = __builtin_ctz(b_r);
+    a.lc = __builtin_ctz(b_c);
+    a.R = h->R;
+    a.C = h->C;
+    a.n_tile_rows = h->n_tile_rows;
+    a.n_tile_cols = h->n_tile_cols;
+    a.n_groups = h->n_groups;
+    a.row_tile0 = h->row_tile0;
+    a.row_mask = h->row_mask;
+
+    // (the plan lands behind the descriptors on the host too)
+    h->gdesc_host = new (std::nothrow) int4[ng + 1];
+    if (!h->gdesc_host) {
+        free_handle(h);
+        return fail(LPV_ERR_ALLOC, "host allocation failed");
+    }
+    e = lpv::launch_pack_plan(a, h, plan_d, s);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(h->gdesc_host, h->gdesc, (ng + 1) * sizeof(int4), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess)
+        e = hipStreamSynchronize(s);
+    if (e != hipSuccess) {
+        free_handle(h);
+        return hip_fail(e, "pack plan");
+    }
+    lpv::Plan plan;
+    memcpy(&plan, h->gdesc_host + ng, sizeof plan);
+    h->nnzb = plan.nnzb;
+    h->n_steps = mfma_path ? plan.n_steps : 0;
+    h->n_tiles = mfma_path ? plan.n_tiles : 0;
+    h->n_walk = mfma_path ? plan.n_walk : 0;
+    if (h->n_tiles >= ((int64_t)1 << 21)) {
+        // the kernels address the tile stream with 32-bit byte offsets
+        const long long nt = (long long)h->n_tiles;
+        free_handle(h);
+        return fail(LPV_ERR_SHAPE, "%lld kept 32 x 32 tiles: at most 2^21 - 1 are supported", nt);
+    }
+
+    // the second buffer: values, the tiles in operand order (and again by tile row), col_idx
+    const size_t b_val = (size_t)h->nnzb * b_r * b_c * es;  // (multiples of 512 bytes)
+    const size_t b_str = (size_t)h->n_tiles * lpv::TILE * lpv::TILE * es;
+    e = dmalloc(&h->data, b_val + b_str * (rows ? 2 : 1) + (size_t)h->nnzb * sizeof(int32_t));
+    if (e != hipSuccess) {
+        free_handle(h);
+        return e == hipErrorOutOfMemory ? fail(LPV_ERR_ALLOC, "device allocation failed")
+                                        : hip_fail(e, "hipMalloc");
+    }
+    if (h->data) {
+        char* p = (char*)h->data;
+        h->values = p;
+        if (h->n_tiles > 0)
+            h->stream_vals = p + b_val;
+        if (rows && h->n_tiles > 0)
+            h->row_vals = p + b_val + b_str;
+        h->col_idx = (int32_t*)(p + b_val + b_str * (rows ? 2 : 1));
+    }
+    e = lpv::launch_pack_fill(a, h, s);
+    if (e == hipSuccess)
+        e = hipStreamSynchronize(s);
+    if (e != hipSuccess) {
+        free_handle(h);
+        return hip_fail(e, "pack fill");
+    }
+    *out = h;
+    return LPV_OK;
 }
 
 }  // namespace
@@ -169,135 +312,11 @@ lpv_status lpv_bsr_pack(const void* W, int64_t ldw, int64_t N, int64_t K, lpv_dt
         return fail(LPV_ERR_INVALID_ARG, "W must be 16-byte aligned with ldw >= K and ldw a "
                                          "multiple of 16 bytes");
 
-    lpv_bsr* h = new (std::nothrow) lpv_bsr();
-    if (!h)
-        return fail(LPV_ERR_ALLOC, "host allocation failed");
-    h->N = N;
-    h->K = K;
-    h->b_r = b_r;
-    h->b_c = b_c;
-    h->R = (int32_t)(N / b_r);
-    h->C = (int32_t)(K / b_c);
-    h->dtype = dt;
-    h->n_tile_rows = (int32_t)((N + lpv::TILE - 1) / lpv::TILE);
-    h->n_tile_cols = (int32_t)((K + lpv::TILE - 1) / lpv::TILE);
-    h->n_groups = (h->n_tile_rows + lpv::GROUP_TILES - 1) / lpv::GROUP_TILES;
-    hipStream_t s = (hipStream_t)stream;
-
-    // one buffer for gdesc (16-byte entries first), half_tiles, row_ptr,
-    // group_order, step_ptr, group_tile0, row_tile0, row_mask and the plan
-    const bool rows = es == 2 && K % (2 * lpv::TILE) == 0 && h->n_tile_cols <= lpv::XS_COLS &&
-                      h->n_tile_rows <= lpv::XS_ROWS;
-    const size_t n_half = (size_t)2 * h->n_groups * (size_t)((h->n_tile_cols + 1) & ~1);
-    const size_t n_meta = 4 * (size_t)h->n_groups + n_half + (size_t)(h->R + 1) +
-                          3 * (size_t)(h->n_groups + 1) + 4 +
-                          (rows ? 2 * (size_t)h->n_tile_rows + 1 : 0);
-    void* meta = nullptr;
-    hipError_t e = dmalloc(&meta, n_meta * sizeof(int32_t));
-    if (e != hipSuccess) {
-        free_handle(h);
-        return e == hipErrorOutOfMemory ? fail(LPV_ERR_ALLOC, "device allocation failed")
-                                        : hip_fail(e, "hipMalloc");
-    }
-    h->meta = meta;
-    e = hipGetDevice(&h->device);
-    if (e != hipSuccess) {
-        free_handle(h);
-        return hip_fail(e, "hipGetDevice");
-    }
-    h->gdesc = (int4*)meta;
-    h->half_tiles = (uint32_t*)(h->gdesc + h->n_groups);
-    h->row_ptr = (int32_t*)(h->half_tiles + n_half);
-    h->group_order = h->row_ptr + (h->R + 1);
-    h->step_ptr = h->group_order + (h->n_groups + 1);
-    h->group_tile0 = h->step_ptr + (h->n_groups + 1);
-    lpv::Plan* plan_d = (lpv::Plan*)(h->group_tile0 + (h->n_groups + 1));
-    if (rows) {
-        h->row_tile0 = (int32_t*)(plan_d + 1);
-        h->row_mask = (uint32_t*)(h->row_tile0 + h->n_tile_rows + 1);
-    }
-
     lpv::PackArgs a = {};
     a.W = W;
     a.ldw = ldw;
-    a.N = N;
-    a.K = K;
-    a.es = es;
-    a.b_r = b_r;
-    a.b_c = b_c;
-    a.R = h->R;
-    a.C = h->C;
     a.mask = mask;
-    a.n_tile_rows = h->n_tile_rows;
-    a.n_tile_cols = h->n_tile_cols;
-    a.n_groups = h->n_groups;
-    a.row_tile0 = h->row_tile0;
-    a.row_mask = h->row_mask;
-
-    lpv::Plan plan = {};
-    const bool mfma_path = dt != LPV_F32;
-    if (mfma_path) {
-        h->gdesc_host = new (std::nothrow) int4[h->n_groups];
-        if (!h->gdesc_host) {
-            free_handle(h);
-            return fail(LPV_ERR_ALLOC, "host allocation failed");
-        }
-    }
-    e = lpv::launch_pack_plan(a, h->row_ptr, h->step_ptr, h->group_tile0, h->group_order,
-                              h->gdesc, plan_d, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(&plan, plan_d, sizeof plan, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess && mfma_path)
-        e = hipMemcpyAsync(h->gdesc_host, h->gdesc, (size_t)h->n_groups * sizeof(int4),
-                           hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess)
-        e = hipStreamSynchronize(s);
-    if (e != hipSuccess) {
-        free_handle(h);
-        return hip_fail(e, "pack plan");
-    }
-    h->nnzb = plan.nnzb;
-    h->n_steps = mfma_path ? plan.n_steps : 0;
-    h->n_tiles = mfma_path ? plan.n_tiles : 0;
-    h->n_walk = mfma_path ? plan.n_walk : 0;
-    if (h->n_tiles >= ((int64_t)1 << 21)) {
-        // the kernels address the tile stream with 32-bit byte offsets
-        const long long nt = (long long)h->n_tiles;
-        free_handle(h);
-        return fail(LPV_ERR_SHAPE, "%lld kept 32 x 32 tiles: at most 2^21 - 1 are supported", nt);
-    }
-
-    const size_t blk = (size_t)b_r * b_c * es;
-    e = dmalloc((void**)&h->col_idx, (size_t)h->nnzb * sizeof(int32_t));
-    if (e == hipSuccess)
-        e = dmalloc(&h->values, (size_t)h->nnzb * blk);
-    if (e == hipSuccess && mfma_path) {
-        e = dmalloc((void**)&h->step_col, (size_t)h->n_steps * sizeof(int32_t));
-        if (e == hipSuccess)
-            e = dmalloc((void**)&h->step_bits, (size_t)h->n_steps * sizeof(int32_t));
-        if (e == hipSuccess)
-            e = dmalloc((void**)&h->step_tile, (size_t)h->n_steps * sizeof(int32_t));
-        if (e == hipSuccess)
-            e = dmalloc((void**)&h->walk, (size_t)h->n_walk * sizeof(int2));
-        if (e == hipSuccess)
-            e = dmalloc(&h->stream_vals, (size_t)h->n_tiles * lpv::TILE * lpv::TILE * es * (rows ? 2 : 1));
-        if (e == hipSuccess && rows && h->n_tiles > 0)
-            h->row_vals = (char*)h->stream_vals + (size_t)h->n_tiles * lpv::TILE * lpv::TILE * es;
-    }
-    if (e != hipSuccess) {
-        free_handle(h);
-        return e == hipErrorOutOfMemory ? fail(LPV_ERR_ALLOC, "device allocation failed")
-                                        : hip_fail(e, "hipMalloc");
-    }
-    e = lpv::launch_pack_fill(a, h, s);
-    if (e == hipSuccess)
-        e = hipStreamSynchronize(s);
-    if (e != hipSuccess) {
-        free_handle(h);
-        return hip_fail(e, "pack fill");
-    }
-    *out = h;
-    return LPV_OK;
+    return pack_weight(a, N, K, dt, b_r, b_c, (hipStream_t)stream, out);
 }
 
 lpv_status lpv_bsr_info_get(const lpv_bsr* h, lpv_bsr_info* out)
@@ -471,36 +490,32 @@ lpv_status lpv_bsr_transpose(const lpv_bsr* h, void* stream, lpv_bsr** out)
         return fail(LPV_ERR_INVALID_ARG, "handle lives on device %d, current device is %d",
                     h->device, dev);
     hipStream_t s = (hipStream_t)stream;
-    const int es = elem_size(h->dtype);
-    // the pruned weight transposed (K x N, row stride N) and the transposed
-    // mask (C x R), built on the device and packed like any weight
-    void* WT = nullptr;
-    void* mT = nullptr;
-    e = dmalloc(&WT, (size_t)(h->K * h->N) * es);
-    if (e == hipSuccess)
-        e = dmalloc(&mT, (size_t)h->R * h->C);
-    if (e != hipSuccess) {
-        (void)hipFree(WT);
+    // the limits of a packed K x N weight (the blocks divide it, the sides fit)
+    if (h->dtype != LPV_F32 && h->N > MAX_K16)
+        return fail(LPV_ERR_SHAPE, "K = %lld: the 16-bit kernels take K <= %lld", (long long)h->N,
+                    (long long)MAX_K16);
+    // the transposed mask and the kept blocks' numbers; pack then gathers the transposed
+    // blocks from the values
+    const size_t nb = (size_t)h->R * h->C;
+    void* maps = nullptr;
+    e = dmalloc(&maps, nb * (sizeof(int32_t) + 1));
+    if (e != hipSuccess)
         return e == hipErrorOutOfMemory ? fail(LPV_ERR_ALLOC, "device allocation failed")
                                         : hip_fail(e, "hipMalloc");
-    }
-    e = hipMemsetAsync(WT, 0, (size_t)(h->K * h->N) * es, s);
-    if (e == hipSuccess)
-        e = hipMemsetAsync(mT, 0, (size_t)h->R * h->C, s);
-    if (e == hipSuccess)
-        e = lpv::launch_transpose_blocks(h, WT, h->N, (uint8_t*)mT, s);
+    int32_t* block = (int32_t*)maps;
+    uint8_t* maskT = (uint8_t*)(block + nb);
+    e = lpv::launch_transpose_maps(h, maskT, block, s);
     lpv_status st = e == hipSuccess ? LPV_OK : hip_fail(e, "transpose launch");
-    if (st == LPV_OK)
-        st = lpv_bsr_pack(WT, h->N, h->K, h->N, (lpv_dtype)h->dtype, h->b_c, h->b_r,
-                          (const uint8_t*)mT, stream, out);
-    const hipError_t es2 = hipStreamSynchronize(s);  // before the buffers are freed
-    (void)hipFree(WT);
-    (void)hipFree(mT);
-    if (st == LPV_OK && es2 != hipSuccess) {
-        lpv_bsr_destroy(*out);
-        *out = nullptr;
-        return hip_fail(es2, "transpose");
+    if (st == LPV_OK) {
+        lpv::PackArgs a = {};
+        a.t_values = (const char*)h->values;
+        a.t_block = block;
+        a.mask = maskT;
+        st = pack_weight(a, h->K, h->N, h->dtype, h->b_c, h->b_r, s, out);
     }
+    if (st != LPV_OK)
+        (void)hipStreamSynchronize(s);  // (a finished pack has waited) before the maps are freed
+    (void)hipFree(maps);
     return st;
 }
 

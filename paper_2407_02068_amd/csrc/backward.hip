@@ -6,7 +6,7 @@
 // passes a gradient to the input nor receives one.  For the pre-activation
 // Z = X W~^T + b and G = dL/dZ (M x N):
 //   dX = G W~         the forward kernel run on the handle of W~^T, which
-//                     k_transpose_blocks + pack build (lpv_bsr_transpose)
+//                     k_transpose_maps + pack build (lpv_bsr_transpose)
 //   dW = G^T X        on the kept blocks only: k_gradw_tiles and
 //                     k_gradw_reduce, or k_gradw_f32 for fp32 handles
 //   db = sum_m G[m]   k_bias_partial + k_bias_reduce
@@ -25,33 +25,23 @@ static __device__ uint4 g_zero_line[1];
 
 // ---------------------------------------------------------------- transpose
 
-// One workgroup per block-row r: every kept block (r, c) of the handle is
-// written transposed into the dense K x N buffer WT (block (c, r) of W~^T),
-// and maskT[c][r] is set.  Everything else in WT and maskT is left as the
-// caller cleared it.
-__global__ __launch_bounds__(256) void k_transpose_blocks(int32_t b_r, int32_t b_c, int32_t R,
-                                                          int32_t es, const int32_t* __restrict__ row_ptr,
-                                                          const int32_t* __restrict__ col_idx,
-                                                          const char* __restrict__ values,
-                                                          char* __restrict__ WT, int64_t ldwt,
-                                                          uint8_t* __restrict__ maskT)
+// One workgroup per block-row r: column r of the transposed mask, and the numbers of
+// the row's kept blocks (left unset where none is kept).
+__global__ __launch_bounds__(256) void k_transpose_maps(int32_t R, int32_t C,
+                                                        const int32_t* __restrict__ row_ptr,
+                                                        const int32_t* __restrict__ col_idx,
+                                                        uint8_t* __restrict__ maskT,
+                                                        int32_t* __restrict__ block)
 {
     const int r = blockIdx.x;
     const int p0 = row_ptr[r], p1 = row_ptr[r + 1];
-    const int nb = b_r * b_c;
-    for (int p = p0; p < p1; ++p) {
+    for (int c = threadIdx.x; c < C; c += 256)
+        maskT[(int64_t)c * R + r] = 0;
+    __syncthreads();
+    for (int p = p0 + threadIdx.x; p < p1; p += 256) {
         const int c = col_idx[p];
-        if (threadIdx.x == 0)
-            maskT[(int64_t)c * R + r] = 1;
-        for (int e = threadIdx.x; e < nb; e += 256) {
-            const int i = e / b_c, j = e - i * b_c;  // W~[r b_r + i][c b_c + j]
-            const char* src = values + ((int64_t)p * nb + e) * es;
-            char* dst = WT + (((int64_t)c * b_c + j) * ldwt + (int64_t)r * b_r + i) * es;
-            if (es == 4)
-                *(uint32_t*)dst = *(const uint32_t*)src;
-            else
-                *(uint16_t*)dst = *(const uint16_t*)src;
-        }
+        maskT[(int64_t)c * R + r] = 1;
+        block[(int64_t)r * C + c] = p;
     }
 }
 
@@ -660,14 +650,11 @@ int device_cus()
 
 }  // namespace
 
-hipError_t launch_transpose_blocks(const lpv_bsr* h, void* WT, int64_t ldwt, uint8_t* maskT,
-                                   hipStream_t s)
+hipError_t launch_transpose_maps(const lpv_bsr* h, uint8_t* maskT, int32_t* block, hipStream_t s)
 {
-    const int es = h->dtype == LPV_F32 ? 4 : 2;
     if (h->R > 0)
-        hipLaunchKernelGGL(k_transpose_blocks, dim3(h->R), dim3(256), 0, s, h->b_r, h->b_c, h->R,
-                           es, (const int32_t*)h->row_ptr, (const int32_t*)h->col_idx,
-                           (const char*)h->values, (char*)WT, ldwt, maskT);
+        hipLaunchKernelGGL(k_transpose_maps, dim3(h->R), dim3(256), 0, s, h->R, h->C,
+                           (const int32_t*)h->row_ptr, (const int32_t*)h->col_idx, maskT, block);
     return hipGetLastError();
 }
 

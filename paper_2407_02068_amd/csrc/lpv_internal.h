@@ -33,7 +33,9 @@ struct lpv_bsr {
     int64_t nnzb;
     int32_t dtype;  // lpv_dtype
     int32_t device;
-    void* meta;  // one allocation: gdesc, row_ptr, group_order, step_ptr, group_tile0, plan
+    void* meta;  // one allocation: the index arrays and the schedule (sizes known before the
+                 // kept count is)
+    void* data;  // one allocation: values, stream_vals, row_vals, col_idx
     // canonical BSR
     int32_t* row_ptr;  // R + 1
     int32_t* col_idx;  // nnzb
@@ -70,10 +72,13 @@ struct lpv_bsr {
 namespace lpv {
 
 struct PackArgs {
-    const void* W;
+    const void* W;  // NULL: the transpose of a packed weight, given by the next two
     int64_t ldw, N, K;
+    const char* t_values;    // that weight's BSR values (blocks b_c x b_r) ...
+    const int32_t* t_block;  // ... and, C x R, each kept block's number among them
     int32_t es;  // element size in bytes
     int32_t b_r, b_c, R, C;
+    int32_t lr, lc;  // log2 of b_r, b_c
     const uint8_t* mask;
     int32_t n_tile_rows, n_tile_cols, n_groups;
     int32_t* row_tile0;  // NULL: no row-major tiles
@@ -81,9 +86,10 @@ struct PackArgs {
 };
 
 // pack.hip
-hipError_t launch_pack_plan(const PackArgs& a, int32_t* row_ptr, int32_t* step_ptr,
-                            int32_t* group_tile0, int32_t* group_order, int4* gdesc, Plan* plan,
-                            hipStream_t s);
+// The counts, and (16-bit types) the schedule: everything that fits the handle's first
+// allocation.  The Plan follows gdesc[n_groups] in memory.
+hipError_t launch_pack_plan(const PackArgs& a, const lpv_bsr* h, Plan* plan, hipStream_t s);
+// The block values, column indices and tile copies, into the second one.
 hipError_t launch_pack_fill(const PackArgs& a, const lpv_bsr* h, hipStream_t s);
 hipError_t launch_unpack(const lpv_bsr* h, void* W_out, int64_t ldw, hipStream_t s);
 
@@ -156,8 +162,8 @@ struct GradWCall {
 };
 // Bytes of the weight-gradient workspace of a handle (any M).
 size_t grad_w_workspace_bytes(const lpv_bsr* h);
-hipError_t launch_transpose_blocks(const lpv_bsr* h, void* WT, int64_t ldwt, uint8_t* maskT,
-                                   hipStream_t s);
+// The transposed mask (C x R) of a handle and its kept blocks' numbers (R x C).
+hipError_t launch_transpose_maps(const lpv_bsr* h, uint8_t* maskT, int32_t* block, hipStream_t s);
 hipError_t launch_grad_w(const lpv_bsr* h, const GradWCall& c, hipStream_t s);
 // Encoder block around the pruned layers (encoder.hip).
 constexpr int LN_MAX_D = 2048;     // widest row of the layer norm
