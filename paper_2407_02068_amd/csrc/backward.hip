@@ -118,24 +118,29 @@ __global__ __launch_bounds__(256) void k_bias_partial(const char* __restrict__ G
 }
 
 // db[n] from the chunks' partial sums in a fixed order: workgroup = 32
-// columns; lane group l (0..7) adds chunks l, l + 8, ... in order, then the 8
-// sums are added in order of l; one rounding.
+// columns; lane group l (0 .. 31) adds chunks l, l + 32, ... in order, then the 32
+// sums are added in order of l; one rounding.  (8 lane groups, 32 dependent rounds
+// of loads for 256 chunks: 8.6 us at N = 3072; this 4.2.)
+constexpr int BR_GROUPS = 32;
 template <int DT>
-__global__ __launch_bounds__(256) void k_bias_reduce(const float* __restrict__ part, int n_chunks,
-                                                     int64_t N, char* __restrict__ db)
+__global__ __launch_bounds__(32 * BR_GROUPS) void k_bias_reduce(const float* __restrict__ part,
+                                                                int n_chunks, int64_t N,
+                                                                char* __restrict__ db)
 {
-    __shared__ float s_sum[8][32];
+    __shared__ float s_sum[BR_GROUPS][32];
     const int col = threadIdx.x & 31, l = threadIdx.x >> 5;
     const int64_t n = (int64_t)blockIdx.x * 32 + col;
     float s = 0.0f;
     if (n < N)
-        for (int c = l; c < n_chunks; c += 8)
+#pragma unroll 8
+        for (int c = l; c < n_chunks; c += BR_GROUPS)
             s += part[(int64_t)c * N + n];
     s_sum[l][col] = s;
     __syncthreads();
     if (l == 0 && n < N) {
         float t = 0.0f;
-        for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int i = 0; i < BR_GROUPS; ++i)
             t += s_sum[i][col];
         store_elem<DT>(db, n, t);
     }
@@ -611,32 +616,42 @@ __global__ __launch_bounds__(GW_NT, 1) void k_gradw_tiles(const GradWDims d,
 // out[p][i][j] (BSR order) = the chunks' partials of element (n, k) =
 // (r b_r + i, c b_c + j) added in chunk order, rounded once.  Accumulator
 // order inside a 32 x 32 tile: element (nn, kk) is lane kk + 32 ((nn / 4) % 2),
-// register 4 (nn / 8) + nn % 4.
+// register 4 (nn / 8) + nn % 4, so a thread takes the four rows of one 16-byte
+// run; a block has at least 64 runs, so its row and column are found once per wave
+// (one thread per element, each with its own search and 4-byte reads, took 16 us for
+// 1152 32 x 32 blocks and 7 chunks; this 8.1).
 template <int DT>
-__global__ __launch_bounds__(256) void k_gradw_reduce(int32_t b_r, int32_t b_c, int32_t R,
+__global__ __launch_bounds__(256) void k_gradw_reduce(int32_t lr, int32_t lc, int32_t R,
                                                       const int32_t* __restrict__ row_ptr,
                                                       const int32_t* __restrict__ col_idx,
-                                                      int64_t total, int32_t n_tile_cols,
+                                                      int64_t runs, int32_t n_tile_cols,
                                                       int64_t chunk_stride, int32_t n_chunks,
                                                       const float* __restrict__ ws,
                                                       char* __restrict__ out)
 {
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= total)
-        return;
-    const int nb = b_r * b_c;
-    const int64_t p = idx / nb;
-    const int e = (int)(idx - p * nb);
+    if (idx >= runs)
+        return;  // (whole waves)
+    const int lb = lr + lc - 2;  // log2 of runs per block
+    const int p = __builtin_amdgcn_readfirstlane((int)(idx >> lb));  // (at most 2^24 blocks)
+    const int e = (int)(idx & ((1 << lb) - 1));
     const int r = block_row(row_ptr, R, p), c = col_idx[p];
-    const int i = e / b_c, j = e - i * b_c;
-    const int64_t n = (int64_t)r * b_r + i, k = (int64_t)c * b_c + j;
-    const int nn = (int)(n & 31), kk = (int)(k & 31);
-    const int64_t off = ((n >> 5) * n_tile_cols + (k >> 5)) * 1024 + (nn >> 3) * 256 +
-                        (kk + 32 * ((nn >> 2) & 1)) * 4 + (nn & 3);
-    float s = 0.0f;
-    for (int ch = 0; ch < n_chunks; ++ch)
-        s += ws[ch * chunk_stride + off];
-    store_elem<DT>(out, idx, s);
+    const int i = (e >> lc) * 4, j = e & ((1 << lc) - 1);  // rows i .. i + 3, column j
+    const int n = (r << lr) + i, k = (c << lc) + j;
+    const float* src = ws + ((int64_t)(n >> 5) * n_tile_cols + (k >> 5)) * 1024 + ((n >> 3) & 3) * 256 +
+                       ((k & 31) + 32 * ((n >> 2) & 1)) * 4;
+    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 8
+    for (int ch = 0; ch < n_chunks; ++ch) {
+        const float4 v = *(const float4*)(src + ch * chunk_stride);
+        s[0] += v.x;
+        s[1] += v.y;
+        s[2] += v.z;
+        s[3] += v.w;
+    }
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+        store_elem<DT>(out, ((int64_t)p << (lr + lc)) + ((int64_t)(i + x) << lc) + j, s[x]);
 }
 
 int device_cus()
@@ -702,11 +717,11 @@ hipError_t bias_grad_kernels(const void* G, int64_t ldg, int64_t M, int64_t N, i
     }
     const dim3 grid((unsigned)((N + 31) / 32));
     if (dtype == LPV_BF16)
-        hipLaunchKernelGGL(k_bias_reduce<LPV_BF16>, grid, dim3(256), 0, s, part, (int)n_chunks, N, (char*)db);
+        hipLaunchKernelGGL(k_bias_reduce<LPV_BF16>, grid, dim3(32 * BR_GROUPS), 0, s, part, (int)n_chunks, N, (char*)db);
     else if (dtype == LPV_F16)
-        hipLaunchKernelGGL(k_bias_reduce<LPV_F16>, grid, dim3(256), 0, s, part, (int)n_chunks, N, (char*)db);
+        hipLaunchKernelGGL(k_bias_reduce<LPV_F16>, grid, dim3(32 * BR_GROUPS), 0, s, part, (int)n_chunks, N, (char*)db);
     else
-        hipLaunchKernelGGL(k_bias_reduce<LPV_F32>, grid, dim3(256), 0, s, part, (int)n_chunks, N, (char*)db);
+        hipLaunchKernelGGL(k_bias_reduce<LPV_F32>, grid, dim3(32 * BR_GROUPS), 0, s, part, (int)n_chunks, N, (char*)db);
     return hipGetLastError();
 }
 
@@ -834,25 +849,26 @@ hipError_t launch_grad_w(const lpv_bsr* h, const GradWCall& c, hipStream_t s)
     hipError_t e = hipSuccess;
     d.per_xcd = (int32_t)((n_win * d.n_chunks + 7) / 8);
     const dim3 grid((unsigned)(8 * d.per_xcd)), block(GW_NT);
-    const dim3 rgrid((unsigned)((total + 255) / 256));
+    const int32_t lr = __builtin_ctz(h->b_r), lc = __builtin_ctz(h->b_c);
+    const dim3 rgrid((unsigned)((total / 4 + 255) / 256));
     if (h->dtype == LPV_BF16) {
         hipLaunchKernelGGL(k_gradw_tiles<LPV_BF16>, grid, block, 0, s, d, (const int32_t*)h->step_ptr,
                            (const int32_t*)h->step_col, (const int32_t*)h->step_bits,
                            (const char*)c.G, (const char*)c.X, ws);
         e = hipGetLastError();
         if (e == hipSuccess)
-            hipLaunchKernelGGL(k_gradw_reduce<LPV_BF16>, rgrid, dim3(256), 0, s, h->b_r, h->b_c,
-                               h->R, (const int32_t*)h->row_ptr, (const int32_t*)h->col_idx,
-                               total, d.n_tile_cols, chunk_stride, d.n_chunks, ws, (char*)c.dW);
+            hipLaunchKernelGGL(k_gradw_reduce<LPV_BF16>, rgrid, dim3(256), 0, s, lr, lc, h->R,
+                               (const int32_t*)h->row_ptr, (const int32_t*)h->col_idx,
+                               total / 4, d.n_tile_cols, chunk_stride, d.n_chunks, ws, (char*)c.dW);
     } else {
         hipLaunchKernelGGL(k_gradw_tiles<LPV_F16>, grid, block, 0, s, d, (const int32_t*)h->step_ptr,
                            (const int32_t*)h->step_col, (const int32_t*)h->step_bits,
                            (const char*)c.G, (const char*)c.X, ws);
         e = hipGetLastError();
         if (e == hipSuccess)
-            hipLaunchKernelGGL(k_gradw_reduce<LPV_F16>, rgrid, dim3(256), 0, s, h->b_r, h->b_c,
-                               h->R, (const int32_t*)h->row_ptr, (const int32_t*)h->col_idx,
-                               total, d.n_tile_cols, chunk_stride, d.n_chunks, ws, (char*)c.dW);
+            hipLaunchKernelGGL(k_gradw_reduce<LPV_F16>, rgrid, dim3(256), 0, s, lr, lc, h->R,
+                               (const int32_t*)h->row_ptr, (const int32_t*)h->col_idx,
+                               total / 4, d.n_tile_cols, chunk_stride, d.n_chunks, ws, (char*)c.dW);
     }
     if (e == hipSuccess)
         e = hipGetLastError();
