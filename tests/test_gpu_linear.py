@@ -88,6 +88,7 @@ def test_fp32_tiles(M, N, K, b_r, b_c):
     (577, 1280, 192, 64, 16),    # 2 x 8: 3 pairs for 8 waves
     (640, 2528, 128, 32, 32),    # 2 x 4: an odd number of tile rows
     (1217, 2512, 192, 16, 32),   # 2 x 2
+    (1217, 1008, 1536, 16, 32),  # 4 x 4 (a long reduction)
     (1889, 2560, 128, 64, 64),   # 4 x 2
     (8255, 752, 1536, 16, 16),   # 4 x 1 (block-sparse; dense: the persistent kernel)
 ])
