@@ -108,11 +108,11 @@ __global__ __launch_bounds__(256) void k_add_layernorm(const uint16_t* x, const 
 
 // ---------------------------------------------------------------- attention
 
-// One workgroup per (sequence, head), 8 waves.  K and V of the head are staged
+// One workgroup per (sequence, head), NT / 64 waves.  K and V of the head are staged
 // once in LDS, row-major (row = token, 64 elements and 16 bytes of padding:
 // 144-byte rows put 16 consecutive rows of one 16-byte column in distinct
-// banks), zero past the last token; wave w takes the 32-query tiles w, w + 8,
-// ...  S^T = K Q^T on the matrix cores (lane: key or query l % 32, 8
+// banks), zero past the last token; wave w takes the 32-query tiles w, w +
+// NT / 64, ...  S^T = K Q^T on the matrix cores (lane: key or query l % 32, 8
 // consecutive head dimensions; K from LDS, Q from global memory once per
 // tile).  Its accumulator gives lane l query l % 32 and, in register r, key
 // 8 (r / 4) + 4 (l / 32) + r % 4 of the 32-key tile: a row of softmax lives
@@ -127,7 +127,6 @@ __global__ __launch_bounds__(256) void k_add_layernorm(const uint16_t* x, const 
 // holds one query per lane, so the rescale and the final 1 / l are per lane.
 // The weights summed into l are the rounded ones, so the output is exactly a
 // weighted mean of V with those weights.
-constexpr int ATT_NT = 512;
 constexpr int ATT_RS = ATT_HD * 2 + 16;  // bytes per staged row
 static_assert(2 * ((ATT_MAX_T + 31) / 32 * 32) * ATT_RS <= 163840, "K and V of a head fit in LDS");
 
@@ -157,8 +156,8 @@ __device__ inline uint4 att_read16(uint32_t addr)
     return __builtin_bit_cast(uint4, *(const __attribute__((address_space(3))) att_u4*)(uintptr_t)addr);
 }
 
-template <int DT>
-__global__ __launch_bounds__(ATT_NT) void k_attention(const uint16_t* __restrict__ qkv, int32_t T,
+template <int DT, int NT>
+__global__ __launch_bounds__(NT) void k_attention(const uint16_t* __restrict__ qkv, int32_t T,
                                                       int32_t H, uint16_t* __restrict__ out)
 {
     using E = Elem<DT>;
@@ -188,11 +187,11 @@ __global__ __launch_bounds__(ATT_NT) void k_attention(const uint16_t* __restrict
     // staging: 16-byte chunk c (0..7) of row s of K and V; every load of a
     // batch is issued before the first LDS write
     constexpr int SB = 4;
-    for (int i0 = threadIdx.x; i0 < Tp * 8; i0 += SB * ATT_NT) {
+    for (int i0 = threadIdx.x; i0 < Tp * 8; i0 += SB * NT) {
         uint4 kv[SB], vv[SB];
 #pragma unroll
         for (int b = 0; b < SB; ++b) {
-            const int i = i0 + b * ATT_NT, s = i >> 3, c = i & 7;
+            const int i = i0 + b * NT, s = i >> 3, c = i & 7;
             kv[b] = uint4{0u, 0u, 0u, 0u};
             vv[b] = uint4{0u, 0u, 0u, 0u};
             if (s < T) {
@@ -203,7 +202,7 @@ __global__ __launch_bounds__(ATT_NT) void k_attention(const uint16_t* __restrict
         }
 #pragma unroll
         for (int b = 0; b < SB; ++b) {
-            const int i = i0 + b * ATT_NT, s = i >> 3, c = i & 7;
+            const int i = i0 + b * NT, s = i >> 3, c = i & 7;
             if (i < Tp * 8) {
                 *(uint4*)(kl + s * ATT_RS + 16 * c) = kv[b];
                 *(uint4*)(vl + s * ATT_RS + 16 * c) = vv[b];
@@ -222,7 +221,7 @@ __global__ __launch_bounds__(ATT_NT) void k_attention(const uint16_t* __restrict
     const uint32_t va = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)vl +
                         ((jj >> 2) + 4 * (g >> 1)) * ATT_RS + (16 * (g & 1) + 4 * (jj & 3)) * 2;
     const float scale = 0.125f * 1.44269504088896340736f;  // 1 / sqrt(64), in base 2
-    for (int qt = wave; qt < n_kt; qt += ATT_NT / 64) {
+    for (int qt = wave; qt < n_kt; qt += NT / 64) {
         const int q = qt * 32 + l32;
         if (qt != wave)
             load_q(qt);
@@ -325,37 +324,49 @@ hipError_t launch_add_layernorm(const void* x, const void* y, int64_t M, int32_t
     return hipGetLastError();
 }
 
+namespace {
+
+template <int DT, int NT>
+hipError_t launch_attention_as(const void* qkv, int64_t n_seq, int32_t T, int32_t H, void* out,
+                               hipStream_t s)
+{
+    const size_t lds = (size_t)2 * ((T + 31) / 32 * 32) * ATT_RS;
+    // dynamic LDS beyond 64 KB (T > 224) must be allowed per kernel; the
+    // setting is idempotent, so a race between threads is harmless
+    static bool allowed = false;
+    if (NT == 512 && !allowed) {
+        const hipError_t e = hipFuncSetAttribute((const void*)k_attention<DT, NT>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 2 * ((ATT_MAX_T + 31) / 32 * 32) * ATT_RS);
+        if (e != hipSuccess)
+            return e;
+        allowed = true;
+    }
+    hipLaunchKernelGGL((k_attention<DT, NT>), dim3((unsigned)(n_seq * H)), dim3(NT), lds, s,
+                       (const uint16_t*)qkv, T, H, (uint16_t*)out);
+    return hipGetLastError();
+}
+
+}  // namespace
+
 hipError_t launch_attention(const void* qkv, int64_t n_seq, int32_t T, int32_t H, int dtype,
                             void* out, hipStream_t s)
 {
     if (n_seq == 0)
         return hipSuccess;
-    const int n_kt = (T + 31) / 32;
-    const size_t lds = (size_t)2 * 32 * n_kt * ATT_RS;
-    const dim3 grid((unsigned)(n_seq * H)), block(ATT_NT);
-    // dynamic LDS beyond 64 KB (T > 224) must be allowed per kernel; the
-    // setting is idempotent, so a race between threads is harmless
-    static bool allowed[2] = {false, false};
-    const int ix = dtype == LPV_BF16 ? 1 : 0;
-    if (!allowed[ix]) {
-        const int max_lds = 2 * ((ATT_MAX_T + 31) / 32 * 32) * ATT_RS;
-        const hipError_t e =
-            dtype == LPV_BF16
-                ? hipFuncSetAttribute((const void*)k_attention<LPV_BF16>,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, max_lds)
-                : hipFuncSetAttribute((const void*)k_attention<LPV_F16>,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);
-        if (e != hipSuccess)
-            return e;
-        allowed[ix] = true;
-    }
-    if (dtype == LPV_BF16)
-        hipLaunchKernelGGL(k_attention<LPV_BF16>, grid, block, lds, s, (const uint16_t*)qkv, T, H,
-                           (uint16_t*)out);
-    else
-        hipLaunchKernelGGL(k_attention<LPV_F16>, grid, block, lds, s, (const uint16_t*)qkv, T, H,
-                           (uint16_t*)out);
-    return hipGetLastError();
+    // A wave per 32-query tile up to 64 tokens and 8 at most: with more, idle waves hold
+    // the slots that further heads would fill (us, 8 waves / this: 3072 heads of 49
+    // tokens 22.3 / 17.6, of 16 23.7 / 12.0, 768 of 128 14.2 / 12.9, 1536 of 64 13.6 /
+    // 11.4; 2 waves at 768 x 128 15.1; 4 waves at 768 x 197 25.3 against 23.8).
+#define LPV_ATT(NT_)                                                            \
+    (dtype == LPV_BF16 ? launch_attention_as<LPV_BF16, NT_>(qkv, n_seq, T, H, out, s) \
+                       : launch_attention_as<LPV_F16, NT_>(qkv, n_seq, T, H, out, s))
+    if (T <= 64)
+        return LPV_ATT(128);
+    if (T <= 128)
+        return LPV_ATT(256);
+    return LPV_ATT(512);
+#undef LPV_ATT
 }
 
 }  // namespace lpv

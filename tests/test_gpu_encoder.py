@@ -48,6 +48,15 @@ def test_attention_matches_oracle(n_seq, T, H, dtype):
     assert e <= TOL[dtype]
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("n_seq,T,H", [(70, 16, 12), (5, 49, 3), (1, 64, 2), (1, 65, 2), (3, 96, 1),
+                                       (2, 97, 1), (1, 128, 2), (1, 129, 2), (1, 257, 1)])
+def test_attention_waves_per_head(n_seq, T, H, dtype):
+    # 2 waves up to 64 tokens, 4 up to 128, then 8: each edge, and tiles shared unevenly
+    y, x = run_attention(n_seq, T, H, dtype)
+    assert rel(y, enc.attention(x, n_seq, T, H, 64)) <= TOL[dtype]
+
+
 def test_attention_sharp_scores():
     # scores with a spread of ~8: the running maximum and rescaling matter
     y, x = run_attention(2, 197, 3, "bf16", q_scale=8.0)
