@@ -149,7 +149,7 @@ def kernel_label(name):
             return key + " (lpv_bsr_pack)"
     for key, api in (("k_gradw_tiles", "lpv_bsr_grad_w"), ("k_gradw_reduce", "lpv_bsr_grad_w"),
                      ("k_gradw_f32", "lpv_bsr_grad_w"), ("k_bias_partial", "lpv_bias_grad"),
-                     ("k_bias_reduce", "lpv_bias_grad"), ("k_transpose_maps", "lpv_bsr_transpose"),
+                     ("k_bias_reduce", "lpv_bias_grad"), ("k_bias_direct", "lpv_bias_grad"), ("k_transpose_maps", "lpv_bsr_transpose"),
                      ("k_unpack", "lpv_bsr_unpack")):
         if key in name:
             return "%s (%s)" % (key, api)

@@ -9,7 +9,7 @@
 //                     k_transpose_maps + pack build (lpv_bsr_transpose)
 //   dW = G^T X        on the kept blocks only: k_gradw_tiles and
 //                     k_gradw_reduce, or k_gradw_f32 for fp32 handles
-//   db = sum_m G[m]   k_bias_partial + k_bias_reduce
+//   db = sum_m G[m]   k_bias_partial + k_bias_reduce, or k_bias_direct
 // Every sum is taken in a fixed order, so results do not depend on timing.
 #include <mutex>
 
@@ -142,6 +142,65 @@ __global__ __launch_bounds__(32 * BR_GROUPS) void k_bias_reduce(const float* __r
 #pragma unroll
         for (int i = 0; i < BR_GROUPS; ++i)
             t += s_sum[i][col];
+        store_elem<DT>(db, n, t);
+    }
+}
+
+// db in one launch and without a workspace, for few tokens: a workgroup takes 128 bytes
+// of columns (whole lines) and all rows; thread = 16 bytes of row g = tid / 8, g + 128, ...
+// (eight rows' loads in flight), then the wave's 8 row groups meet by shuffles and the 16
+// waves in LDS, in a fixed order.  Bound: latency of one pass, and what a CU can load.
+// Up to 4096 rows: 25 - 26 us per call for the chunks (two launches and a stream-ordered
+// allocation and free, host time), 8 - 11 us for this at 192 to 3072 columns.  Above, few
+// workgroups load too slowly: 6304 rows of 3072 in bf16 17 us, 12608 31 us, against 10
+// and 19 us of GPU time for the chunks.
+constexpr int64_t BIAS_DIRECT_ROWS = 4096;
+template <int DT>
+__global__ __launch_bounds__(1024) void k_bias_direct(const char* __restrict__ G, int64_t ldg,
+                                                      int64_t M, int64_t N, char* __restrict__ db)
+{
+    constexpr int ES = DT == LPV_F32 ? 4 : 2, V = 16 / ES, RG = 128, U = 8;
+    __shared__ float s_sum[16][8 * V];
+    const int c = threadIdx.x & 7;
+    const int64_t n0 = ((int64_t)blockIdx.x * 8 + c) * V;
+    float acc[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i)
+        acc[i] = 0.0f;
+    if (n0 + V <= N) {
+        for (int64_t m = threadIdx.x >> 3; m < M; m += U * RG) {
+            v4u v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)  // (rows past M repeat the last and are not added)
+                v[u] = *(const v4u*)(G + (min(m + u * RG, M - 1) * ldg + n0) * ES);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (m + u * RG < M)
+#pragma unroll
+                    for (int i = 0; i < V; ++i)
+                        acc[i] += load_elem<DT>((const char*)&v[u], i);
+        }
+    } else {
+        for (int64_t m = threadIdx.x >> 3; m < M; m += RG)
+            for (int i = 0; i < V; ++i)
+                if (n0 + i < N)
+                    acc[i] += load_elem<DT>(G, m * ldg + n0 + i);
+    }
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        acc[i] += __shfl_xor(acc[i], 8, 64);
+        acc[i] += __shfl_xor(acc[i], 16, 64);
+        acc[i] += __shfl_xor(acc[i], 32, 64);
+        if ((threadIdx.x & 63) < 8)
+            s_sum[threadIdx.x >> 6][c * V + i] = acc[i];
+    }
+    __syncthreads();
+    const int64_t n = (int64_t)blockIdx.x * 8 * V + threadIdx.x;
+    if (threadIdx.x < 8 * V && n < N) {
+        float t = 0.0f;
+#pragma unroll
+        for (int w = 0; w < 16; ++w)
+            t += s_sum[w][threadIdx.x];
         store_elem<DT>(db, n, t);
     }
 }
@@ -738,9 +797,29 @@ hipError_t scratch_err[MAX_DEVICES];
 
 }  // namespace
 
+// One launch without a workspace (k_bias_direct), in place of the chunks.
+static hipError_t launch_bias_direct(const void* G, int64_t ldg, int64_t M, int64_t N, int dtype,
+                                     void* db, hipStream_t s)
+{
+    const int64_t cols = dtype == LPV_F32 ? 32 : 64;
+    const dim3 grid((unsigned)((N + cols - 1) / cols)), block(1024);
+#define LPV_BIAS_DIRECT(DT_) \
+    hipLaunchKernelGGL(k_bias_direct<DT_>, grid, block, 0, s, (const char*)G, ldg, M, N, (char*)db)
+    if (dtype == LPV_BF16)
+        LPV_BIAS_DIRECT(LPV_BF16);
+    else if (dtype == LPV_F16)
+        LPV_BIAS_DIRECT(LPV_F16);
+    else
+        LPV_BIAS_DIRECT(LPV_F32);
+#undef LPV_BIAS_DIRECT
+    return hipGetLastError();
+}
+
 hipError_t launch_bias_grad(const void* G, int64_t ldg, int64_t M, int64_t N, int dtype, void* db,
                             hipStream_t s)
 {
+    if (M <= BIAS_DIRECT_ROWS)
+        return launch_bias_direct(G, ldg, M, N, dtype, db, s);
     int64_t rows = 0;
     const int64_t n_chunks = bias_chunks(M, N, dtype == LPV_F32 ? 4 : 8, (int64_t)1 << 40, &rows);
     float* part = nullptr;
@@ -755,6 +834,8 @@ hipError_t launch_bias_grad(const void* G, int64_t ldg, int64_t M, int64_t N, in
 hipError_t launch_bias_grad_noalloc(const void* G, int64_t ldg, int64_t M, int64_t N, int dtype,
                                     void* db, hipStream_t s)
 {
+    if (M <= BIAS_DIRECT_ROWS)
+        return launch_bias_direct(G, ldg, M, N, dtype, db, s);
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess)

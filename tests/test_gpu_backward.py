@@ -110,6 +110,20 @@ def test_backward_partial_group(dtype, N, sparsity):
     check_all(w, G, "partial group")
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("M,N", [(1, 16), (127, 72), (129, 196), (1024, 33), (1025, 64), (4096, 100),
+                                 (4097, 100)])
+def test_bias_grad_direct(M, N, dtype):
+    # one launch up to 4096 rows (128 row groups, 8 rows each at a time), chunks above;
+    # ragged columns, rows further apart than they are long
+    G = wl.grad_output(121, 0, M, N, dtype)
+    wide = torch.full((M, (N + 15) // 8 * 8), 1e4, dtype=dev(G, dtype).dtype, device="cuda")
+    wide[:, :N] = dev(G, dtype)
+    db = lpv.bias_grad(wide[:, :N])
+    torch.cuda.synchronize()
+    assert_close(f64(db), oracle.grad_bias(G, dtype), dtype, "bias grad %d x %d" % (M, N))
+
+
 def test_backward_m0():
     w, G = case(4, 256, 256, 32, 32, "bf16", cfg=95)
     h = lpv.bsr_pack(dev(w.W, "bf16"), dev(w.mask), 32, 32)
