@@ -32,7 +32,8 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "bsr_linear_fc1_hbm_traffic.json")
 CLOCK_FILE = os.path.join(ROOT, "profiles", "bsr_linear_fc1_gpu_clock.md")
 STATS_FILE = os.path.join(ROOT, "profiles", "bsr_linear_deit_b_fc1_bf16_kernel_stats.md")
 STATS_FILE_BACKWARD = os.path.join(ROOT, "profiles", "backward_delta_deit_b_fc1_bf16_kernel_stats.md")
-KERNEL_SOURCES = ("paper_2407_02068_amd/csrc/linear.hip", "paper_2407_02068_amd/csrc/lpv_device.h",
+KERNEL_SOURCES = ("paper_2407_02068_amd/csrc/stationary.hip", "paper_2407_02068_amd/csrc/linear.hip",
+                  "paper_2407_02068_amd/csrc/lpv_device.h", "paper_2407_02068_amd/csrc/lpv_lds.h",
                   "paper_2407_02068_amd/csrc/lpv_internal.h")
 
 
@@ -66,9 +67,9 @@ def algorithmic_bytes(M, N, K, nnzb, b_r, b_c, kused_cols, es=2):
     return es * (M * kused_cols + M * N + nnzb * b_r * b_c + N) + 4 * (N // b_r + 1 + nnzb)
 
 
-# bf16, no GELU, block-sparse with 32-wide blocks / dense; 12 groups of 256
-# outputs, so the pair's last k-step is multiplied after its barrier
-SPARSE_KERNEL = "k_linear16<2, false, false, false, false, true>"
+# bf16, no GELU: block-sparse with X in registers (24 column tiles) / dense, 12 groups
+# of 256 outputs, so the pair's last k-step is multiplied after its barrier
+SPARSE_KERNEL = "k_linear16_xs<2, false, 24>"
 DENSE_KERNEL = "k_linear16<2, false, true, false, false, true>"
 CALIB_BYTES = 1 << 30                        # the calibration copy reads and writes this much
 
@@ -92,7 +93,7 @@ def write_traffic(fetch_csv, write_csv, command):
     wk, wc = per_dispatch(write_csv, "WRITE_SIZE")
     f_scale = CALIB_BYTES / (fc * 1024.0)
     w_scale = CALIB_BYTES / (wc * 1024.0)
-    out = {"kernel": "k_linear16 (lpv_bsr_linear), bf16, no GELU",
+    out = {"kernel": "k_linear16_xs (lpv_bsr_linear), bf16, no GELU",
            "workload": "DeiT-B fc1 batch 256, 32x32 blocks, 50% block sparsity",
            "kernel_source_sha256_16": kernel_source_hash(),
            "fetch_kib_per_dispatch": round(fk, 1), "write_kib_per_dispatch": round(wk, 1),
@@ -126,13 +127,26 @@ def kernel_label(name):
             ", 16-column halves" if m.group(5) == "true" else "",
             ", DMA before the last k-step" if m.group(6) == "false" else "",
             "lpv_dense_linear" if m.group(3) == "true" else "lpv_bsr_linear")
-    labels = (("k_block_scores_lds<2, true", "k_block_scores_lds, Taylor (lpv_delta_curve)"),
+    m = re.search(r"k_linear16_xs<(\d), (true|false), (\d+)>", name)
+    if m:
+        return "k_linear16_xs %s%s, up to %s columns (lpv_bsr_linear)" % (
+            {"2": "bf16", "1": "fp16"}[m.group(1)], " + GELU" if m.group(2) == "true" else "",
+            32 * int(m.group(3)))
+    m = re.search(r"k_linear16_split<(\d), (true|false), (true|false), (\d), (\d)>", name)
+    if m:
+        return "k_linear16_split %s %s%s, %s rows x %s waves (%s)" % (
+            {"2": "bf16", "1": "fp16"}[m.group(1)],
+            "dense" if m.group(3) == "true" else "block-sparse",
+            " + GELU" if m.group(2) == "true" else "", m.group(4), m.group(5),
+            "lpv_dense_linear" if m.group(3) == "true" else "lpv_bsr_linear")
+    labels = (("k_linear_f32", "k_linear_f32 (linear, fp32)"),
+              ("k_block_scores_lds<2, true", "k_block_scores_lds, Taylor (lpv_mask_topk)"),
               ("k_block_scores_lds<2, false", "k_block_scores_lds, sum of squares (lpv_mask_topk)"),
               ("k_block_scores<2, true", "k_block_scores, Taylor (lpv_delta_curve)"),
               ("k_block_scores<2, false", "k_block_scores, sum of squares (lpv_mask_topk)"),
               ("k_block_scores", "k_block_scores (lpv_mask_topk)"),
               ("k_delta_dots", "k_delta_dots (lpv_delta_curve)"),
-              ("k_rank", "k_rank (lpv_delta_curve)"),
+              ("k_rank", "k_rank (lpv_mask_topk, lpv_delta_curve)"),
               ("k_delta_steps", "k_delta_steps (lpv_delta_curve)"),
               ("k_delta_finish", "k_delta_finish (lpv_delta_curve)"),
               ("k_mask_topk", "k_mask_topk (lpv_mask_topk)"),
@@ -218,10 +232,10 @@ def write_stats(stats_csv, command, backward=False, trace_csv=None, bench_log=No
             kernel_label(r["Name"]), r["Calls"], float(r["AverageNs"]) / 1e3,
             float(r["MinNs"]) / 1e3, float(r["MaxNs"]) / 1e3, float(r["Percentage"])))
     if backward:
-        text += ["", "The block-sparse k_linear16 row counts the forward launches and the dX "
-                 "launches (the same kernel on the transposed handle).  dW is k_gradw_tiles + "
+        text += ["", "The forward launches are the k_linear16_xs row, dX the block-sparse k_linear16 "
+                 "or k_linear16_split one (on the transposed handle).  dW is k_gradw_tiles + "
                  "k_gradw_reduce, db k_bias_partial + k_bias_reduce, the delta curve "
-                 "k_block_scores_lds + k_rank + k_delta_dots + "
+                 "k_delta_dots (scores too) + k_rank + "
                  "k_delta_steps + k_delta_finish; Cijk_Ailk is hipBLASLt's dense G^T X "
                  "reference, Custom_Cijk_Alik its dense forward."]
     else:
@@ -300,7 +314,7 @@ def write_counters(csvs, command):
         text.append("rocprofv3 --pmc %s -d gpurun_out/pmc_c%d -o c%d --output-format csv -- "
                     "python bench.py --profile-pass" % (c, i + 1, i + 1))
     text += [command, "```", "",
-             "| figure | k_linear16 block-sparse | k_linear16 dense |", "|---|---:|---:|"]
+             "| figure | k_linear16_xs block-sparse | k_linear16 dense |", "|---|---:|---:|"]
     for (name, a), (_, b) in zip(derived("bsr"), derived("dense")):
         text.append("| %s | %s | %s |" % (name, a, b))
     text += ["", "Counter values are per dispatch, averaged over the three launches; SQ counters "
@@ -321,7 +335,7 @@ def write_clock(csv_path, command):
     n_xcc = max(int(a.get("Num_Xcc") or 0) for a in csv.DictReader(open(agents)))
     rows = [r for r in csv.DictReader(open(csv_path)) if r["Counter_Name"] == "GRBM_GUI_ACTIVE"]
     lines = []
-    for name, key in (("k_linear16 bf16 block-sparse (lpv_bsr_linear)", SPARSE_KERNEL),
+    for name, key in (("k_linear16_xs bf16 block-sparse (lpv_bsr_linear)", SPARSE_KERNEL),
                       ("k_linear16 bf16 dense (lpv_dense_linear)", DENSE_KERNEL)):
         sel = [r for r in rows if key in r["Kernel_Name"]]
         if not sel:
@@ -1055,7 +1069,7 @@ def main():
         "roofline": {"bound": "mfma", "achieved": round(achieved, 1), "peak": PEAK_BF16_TFLOPS,
                      "unit": "TFLOP/s", "frac": round(achieved / PEAK_BF16_TFLOPS, 4),
                      "traffic": traffic,
-                     "kernel": "k_linear16 (lpv_bsr_linear)",
+                     "kernel": "k_linear16_xs (lpv_bsr_linear)",
                      "achieved_from": "kept FLOPs / mean HIP-event duration of the %d timed steps"
                                       % args.steps,
                      "hbm_alg_bytes": alg_bytes, "hbm_achieved_GBs": round(hbm_gbs, 1),
