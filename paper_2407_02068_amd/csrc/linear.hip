@@ -815,6 +815,13 @@ struct SplitDims {
 constexpr int SPL_BM = 64;          // tokens per workgroup
 constexpr int SPL_MAX_PAIRS = 128;  // column pairs (K at most 8192)
 
+// Runs per round of the exchange of partial sums: a wave's `runs` (a power of two)
+// halved until a round fits the `room` runs that the stages hold per wave.
+constexpr int exchange_round(int runs, int room)
+{
+    return runs <= room ? runs : exchange_round(runs / 2, room);
+}
+
 template <int DT, bool GELU, bool DENSE, int RT, int WV>
 __global__ __launch_bounds__(64 * WV) void k_linear16_split(
     const SplitDims a, const char* __restrict__ X, const char* __restrict__ stream,
@@ -827,8 +834,10 @@ __global__ __launch_bounds__(64 * WV) void k_linear16_split(
     constexpr int RING = WV * SB;
     constexpr int QN = RT * 8, QW = QN / WV; // 4-register runs of the accumulators; per finishing wave
     constexpr int OS = RT * 64 + 16;         // bytes per token of the output tile in LDS
-    constexpr int ROUND = RING / (WV * 1024) < QN ? RING / (WV * 1024) : QN;
+    constexpr int ROUND = exchange_round(QN, RING / (WV * 1024));
     static_assert(SPL_BM * OS <= RING && QN % WV == 0, "the epilogue reuses the stages");
+    static_assert(QN % ROUND == 0 && ROUND % WV == 0, "whole rounds of the exchange, shared out evenly");
+    static_assert(WV * ROUND * 1024 <= RING, "a round of the exchange fits the stages");
     __shared__ uint4 smem[RING / 16];
 
     const int tid = threadIdx.x, lane = tid & 63;
