@@ -20,6 +20,7 @@
 //   k_delta_finish one workgroup: the update, step by step
 // All sums run in a fixed order (float64), so results do not depend on timing.
 #include "lpv_device.h"
+#include "lpv_grid.h"
 #include "lpv_internal.h"
 #include "lpv_scores.h"
 
@@ -73,14 +74,17 @@ __global__ __launch_bounds__(256) void k_delta_dots(const DeltaCall c, int32_t R
     extern __shared__ double2 s_dyn[];
     double* s_part = (double*)s_dyn;  // VPW x G x nch chunk sums
     constexpr int ES = DT == LPV_F32 ? 4 : 2;
-    if ((int)blockIdx.x < score_wgs) {
+    const int64_t id = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    if (id < score_wgs) {
         wg_block_scores<DT, true, 256>((const char*)c.W, c.ldw, (const char*)c.grad, c.ldg, C, c.b_r,
-                                       c.b_c, score_nb, blockIdx.x, s_dyn, scores);
+                                       c.b_c, score_nb, id, s_dyn, scores);
         return;
     }
-    const int64_t wg = (int64_t)blockIdx.x - score_wgs;
+    const int64_t wg = id - score_wgs;
     const int r = (int)(wg % R);
     const int64_t nv = c.n_samples + 2, v0 = wg / R * VPW;
+    if (v0 >= nv)
+        return;  // (the whole workgroup: past the last one, in the grid's last row)
     const int nvv = (int)min((int64_t)VPW, nv - v0);
     const char* xs[VPW];
     int64_t lx[VPW];
@@ -278,7 +282,8 @@ hipError_t launch_delta_curve(const DeltaCall& c, hipStream_t s)
         const int snb = min(max(1, DELTA_SC_LDS / bytes), C);
         const int64_t score_wgs = (int64_t)R * ((C + snb - 1) / snb);
         const int64_t dot_wgs = (int64_t)R * ((nv + vpw - 1) / vpw);
-        const dim3 grid((unsigned)(score_wgs + dot_wgs));
+        const Grid2 g = grid_of(score_wgs + dot_wgs);
+        const dim3 grid(g.x, g.y);
         const int64_t s_lds = (int64_t)snb * (bytes + 16), d_lds = part * vpw;
         const size_t lds = (size_t)(s_lds > d_lds ? s_lds : d_lds);
 #define LPV_DOTS(DT_)                                                                            \

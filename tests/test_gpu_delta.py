@@ -144,3 +144,21 @@ def test_delta_curve_queued_calls_on_a_side_stream():
         err = np.abs(got.cpu().numpy() - ref).max() / max(np.abs(ref).max(), 1e-300)
         say("delta_curve queued", (b_r, b_c), "rel err %.2e" % err)
         assert err <= TOL
+
+
+@pytest.mark.parametrize("n_s", [1100, 16400])
+def test_delta_curve_many_workgroups(n_s):
+    # more workgroups than a row of the grid (2^20), and more than the 2^24 - 1 of 256 threads
+    # that one grid dimension can hold (34 GB of samples).  All samples but six are
+    # zero: they count in the mean only, so the oracle takes the six, scaled by their share
+    N, K, pcts = 65536, 16, [0, 40, 75, 100]
+    W, grad, few = inputs(114, N, K, 6, "bf16")
+    at = [0, 1, 3, n_s // 2, n_s - 2, n_s - 1]
+    S = torch.zeros((n_s, N, K), dtype=torch.bfloat16, device="cuda")
+    S[at] = dev(few.reshape(6, -1), "bf16").reshape(few.shape)
+    say("delta_curve workgroups", N, K, "n=%d" % n_s)
+    got = lpv.delta_curve(dev(W, "bf16"), dev(grad, "bf16"), S, 16, 16, 0.0, pcts).cpu().numpy()
+    del S
+    none = oracle.delta_curve(W, "bf16", 16, 16, grad, few[:0], 0.0, pcts)
+    ref = none + (oracle.delta_curve(W, "bf16", 16, 16, grad, few, 0.0, pcts) - none) * 6 / n_s
+    assert np.abs(got - ref).max() <= TOL * np.abs(ref).max()
