@@ -16,6 +16,7 @@
 #include <type_traits>
 
 #include "lpv_device.h"
+#include "lpv_grid.h"
 #include "lpv_internal.h"
 
 namespace lpv {
@@ -293,8 +294,9 @@ __global__ __launch_bounds__(64 * GWF_WAVES) void k_gradw_f32(int32_t b_r, int32
     // sub-tiles in BSR order, a contiguous run to each XCD (workgroup b runs on
     // XCD b % 8): an XCD's L2 then holds the G columns of its block rows
     const int scsh = __builtin_ctz(b_c / (16 * VC)), subsh = __builtin_ctz(b_r / (16 * VR)) + scsh;
-    const int64_t item = (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    if (item >= tiles)
+    const int64_t id = (int64_t)blockIdx.y * gridDim.x + blockIdx.x, per_xcd = (tiles + 7) / 8;
+    const int64_t item = (id & 7) * per_xcd + (id >> 3);
+    if (id >= 8 * per_xcd || item >= tiles)
         return;  // (the whole workgroup)
     const int64_t p = item >> subsh;
     const int sub = (int)(item - (p << subsh));
@@ -891,7 +893,8 @@ hipError_t launch_grad_w(const lpv_bsr* h, const GradWCall& c, hipStream_t s)
         const bool wide = t32 >= (int64_t)device_cus();
         const int vr = wide && h->b_r >= 32 ? 2 : 1, vc = wide && h->b_c >= 32 ? 2 : 1;
         const int64_t tiles = total / (256 * vr * vc);
-        const dim3 grid((unsigned)((tiles + 7) / 8 * 8)), block(64 * GWF_WAVES);  // (at most 2^24 sub-tiles)
+        const Grid2 g = grid_of((tiles + 7) / 8 * 8);  // (up to 2^24 sub-tiles)
+        const dim3 grid(g.x, g.y), block(64 * GWF_WAVES);
 #define LPV_GWF(VR_, VC_)                                                                          \
     hipLaunchKernelGGL((k_gradw_f32<VR_, VC_>), grid, block, 0, s, h->b_r, h->b_c, h->R,           \
                        (const int32_t*)h->row_ptr, (const int32_t*)h->col_idx, (const float*)c.G,  \

@@ -100,6 +100,22 @@ def test_backward_fp32_tiles(M, N, K, b_r, b_c):
     check_all(w, G, "fp32 tiles")
 
 
+@pytest.mark.parametrize("N,K", [(16384, 16400), (65536, 32768)])
+def test_backward_fp32_many_blocks(N, K):
+    # more 16 x 16 sub-tiles than a row of the grid (2^20), and as many (2^23, 8 GB of
+    # gradients) as one grid dimension cannot hold.  One token: each element is a single
+    # product, exact
+    say("backward fp32 blocks", N, K)
+    h = lpv.bsr_pack(torch.zeros((N, K), device="cuda"),
+                     torch.ones((N // 16, K // 16), dtype=torch.uint8, device="cuda"), 16, 16)
+    G, X = torch.randn((1, N), device="cuda"), torch.randn((1, K), device="cuda")
+    dW = lpv.grad_w(h, G, X).reshape(N // 16, K // 16, 16, 16)
+    for i in range(0, N // 16, 256):
+        g, x = G[0, 16 * i:16 * (i + 256)].reshape(-1, 1, 16, 1), X.reshape(1, -1, 1, 16)
+        assert torch.equal(dW[i:i + 256], g * x)
+    h.close()
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("N,sparsity", [(384, 0), (384, 50), (192, 30), (512, 60)])
 def test_backward_partial_group(dtype, N, sparsity):
