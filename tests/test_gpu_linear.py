@@ -81,6 +81,25 @@ def test_fp32_tiles(M, N, K, b_r, b_c):
     assert_close(f64(Yd), r, "f32", "dense")
 
 
+@pytest.mark.parametrize("M", [2**26 + 24, 2**30 - 256])
+def test_fp32_many_tokens(M):
+    # more token tiles (64 tokens) than a row of the grid (2^20), and as many as bring one grid
+    # dimension to its limit once rounded up to the 8 XCDs (128 GiB of X and Y).  The
+    # identity as weight: Y is X
+    if torch.cuda.mem_get_info()[0] < 150 * M:
+        pytest.skip("needs %d GB of free device memory" % (150 * M // 10**9))
+    say("fp32 tokens", M)
+    h = lpv.bsr_pack(torch.eye(16, device="cuda"),
+                     torch.ones((1, 1), dtype=torch.uint8, device="cuda"), 16, 16)
+    X = torch.randn((M, 16), device="cuda")
+    Y = torch.full_like(X, 7.0)
+    lpv.bsr_linear(h, X, Y=Y)
+    for i in range(0, M, 2**27):
+        assert torch.equal(Y[i:i + 2**27], X[i:i + 2**27])
+    del X, Y
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("dense", [False, True])
 @pytest.mark.parametrize("M,N,K,b_r,b_c", [
     (1, 16, 64, 16, 16),         # 1 row x 8 waves: one pair of columns, 16 outputs
