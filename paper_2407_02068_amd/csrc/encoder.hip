@@ -10,6 +10,7 @@
 #include <math.h>
 
 #include "lpv_device.h"
+#include "lpv_grid.h"
 #include "lpv_internal.h"
 
 namespace lpv {
@@ -31,7 +32,7 @@ __global__ __launch_bounds__(256) void k_add_layernorm(const uint16_t* x, const 
                                                        float eps, uint16_t* S, uint16_t* out)
 {
     using E = Elem<DT>;
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t row = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (row >= M)
         return;
@@ -157,13 +158,16 @@ __device__ inline uint4 att_read16(uint32_t addr)
 }
 
 template <int DT, int NT>
-__global__ __launch_bounds__(NT) void k_attention(const uint16_t* __restrict__ qkv, int32_t T,
-                                                      int32_t H, uint16_t* __restrict__ out)
+__global__ __launch_bounds__(NT) void k_attention(const uint16_t* __restrict__ qkv, int32_t heads,
+                                                  int32_t T, int32_t H, uint16_t* __restrict__ out)
 {
     using E = Elem<DT>;
     using F = typename E::frag;
     extern __shared__ uint4 att_lds[];  // K rows, then V rows
-    const int seq = blockIdx.x / H, h = blockIdx.x - seq * H;
+    const int64_t id = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    if (id >= heads)
+        return;  // (the whole workgroup)
+    const int seq = (int)id / H, h = (int)id - seq * H;
     const int n_kt = (T + 31) / 32, Tp = 32 * n_kt;
     const int64_t ld = 3 * (int64_t)H * ATT_HD, ldo = (int64_t)H * ATT_HD;
     const uint16_t* base = qkv + (int64_t)seq * T * ld;
@@ -296,7 +300,8 @@ hipError_t launch_add_layernorm(const void* x, const void* y, int64_t M, int32_t
 {
     if (M == 0)
         return hipSuccess;
-    const dim3 grid((unsigned)((M + 3) / 4)), block(256);
+    const Grid2 g = grid_of((M + 3) / 4);
+    const dim3 grid(g.x, g.y), block(256);
 #define LPV_LN(DT_, NC_)                                                                        \
     hipLaunchKernelGGL((k_add_layernorm<DT_, NC_>), grid, block, 0, s, (const uint16_t*)x,       \
                        (const uint16_t*)y, M, D, (const uint16_t*)gamma, (const uint16_t*)beta, \
@@ -342,8 +347,10 @@ hipError_t launch_attention_as(const void* qkv, int64_t n_seq, int32_t T, int32_
             return e;
         allowed = true;
     }
-    hipLaunchKernelGGL((k_attention<DT, NT>), dim3((unsigned)(n_seq * H)), dim3(NT), lds, s,
-                       (const uint16_t*)qkv, T, H, (uint16_t*)out);
+    const int64_t heads = n_seq * H;  // (below 2^31)
+    const Grid2 g = grid_of(heads);
+    hipLaunchKernelGGL((k_attention<DT, NT>), dim3(g.x, g.y), dim3(NT), lds, s,
+                       (const uint16_t*)qkv, (int32_t)heads, T, H, (uint16_t*)out);
     return hipGetLastError();
 }
 

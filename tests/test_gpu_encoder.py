@@ -222,3 +222,22 @@ def test_encoder_chain_graph_replays(sparse):
         assert torch.equal(xg.view(torch.int16), x_ref.view(torch.int16)), "replay %d: x" % i
         assert torch.equal(Ag.view(torch.int16), A_ref.view(torch.int16)), "replay %d: A" % i
     chain.close()
+
+
+def test_more_rows_and_heads_than_one_grid_dimension_holds():
+    # 2^32 and more threads: one wave per row of the layer norm (here of a constant, whose
+    # norm is beta), two waves per head (one token, whose weight is 1: the output is V)
+    M = 2**26 + 5
+    say("layer norm rows", M)
+    x = torch.full((M, 4), 3.0, dtype=torch.bfloat16, device="cuda")
+    beta = torch.arange(1, 5, dtype=torch.bfloat16, device="cuda")
+    out = lpv.add_layernorm(x, None, torch.ones_like(beta), beta, 1e-6)
+    assert torch.equal(out, beta.expand(M, 4))
+    del x, out
+    n_seq, H = 2**23 + 3, 4
+    say("attention heads", n_seq * H)
+    qkv = torch.randn((n_seq, 3 * 64 * H), dtype=torch.bfloat16, device="cuda")
+    out = torch.zeros((n_seq, 64 * H), dtype=torch.bfloat16, device="cuda")
+    lpv.attention(qkv, n_seq, 1, H, out=out)
+    for i in range(0, n_seq, 2**20):
+        assert torch.equal(out[i:i + 2**20], qkv[i:i + 2**20, 2 * 64 * H:])
