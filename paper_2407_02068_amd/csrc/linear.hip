@@ -1255,24 +1255,45 @@ int64_t split_units(const Dims& d)
     return (d.M + SPL_BM - 1) / SPL_BM * d.n_tile_rows;
 }
 
-// Whether k_linear16_split takes a product: its units must leave k_linear16's
-// persistent workgroups short of items.  GPU time of both at 50% sparsity
-// (bf16, 32 x 32 blocks, us, split / k_linear16): K = 768: 394 tokens x 3072 7 / 20,
-// 1576 x 3072 (2400 units) 16 / 21, 3152 x 3072 (4800) 24 / 22, 6304 x 3072
-// 41 / 37; K = 384: 3152 x 1536 (2400) 12 / 13, 6304 x 1536 19 / 14.  With few
-// groups and a long reduction k_linear16 stays short of items for longer: K =
-// 3072, 768 outputs: 6304 tokens (2376 units) 31 / 67, 12608 53 / 66, 25216
-// (9456) 101 / 120, 50432 238 / 206; K = 1536, 384 outputs: 25216 tokens (4728)
-// 35 / 38, 50432 (9456) 61 / 66.  Dense, K = 3072: 6304 tokens 50 / 79, 12608
-// 90 / 81.
-constexpr int64_t SPL_UNITS = 3072, SPL_UNITS_LONG = 10240;
-bool use_split(const Dims& d, bool dense)
+// The same with the tile rows filled up to the 4-row workgroups of larger products.
+int64_t split_units4(const Dims& d)
+{
+    return (d.M + SPL_BM - 1) / SPL_BM * ((d.n_tile_rows + 3) / 4 * 4);
+}
+
+// Whether k_linear16_split takes a product with n_tiles kept tiles (GPU us, bf16, 50% of
+// 32 x 32 blocks if not said otherwise, split / k_linear16).
+// - Up to 2048 units k_linear16's persistent workgroups are short of items: 2661 sizes of
+//   64 to 5120 outputs and columns, every block shape, 0 to 95% sparsity, took 0.07 to 0.95
+//   of its time.
+// - The 4-row workgroups above take three places on a CU: 3072 units with the rows filled
+//   up run side by side (192 x 192, 64 x 64 blocks: 2760 9.5 / 11.5, 3128 13.6 / 9.9).
+//   Dense (no dropped tile) the line comes earlier, and not at all for a short reduction
+//   (1024 x 64: 14.3 / 8.9; 1536 x 384, 2640 units: 20.9 / 15.9; 2304 x 768, 2232: 27.4 /
+//   25.0; 4096 x 2304, 3072: 54 / 125, two launches).
+// - Few groups and a long reduction leave k_linear16 short of items for longer.  While it
+//   needs one round, up to 5000 units (768 x 3072: 4728 units 53 / 66, 7104 99 / 71, 16 x 16
+//   blocks 136 / 79); its second round costs as much as the first, so up to 10240
+//   (9456 units 99 / 118), unless most tiles are kept (384 x 1536, 7440 units, 41% of the
+//   tiles 60 / 67, 99% 83 / 75).
+constexpr int64_t SPL_UNITS = 2048, SPL_UNITS4 = 3072;
+bool use_split(const Dims& d, bool dense, int64_t n_tiles)
 {
     // whole pairs of column tiles, at most one per lane and table half
     if (d.K % (2 * TILE) || d.K / (2 * TILE) > SPL_MAX_PAIRS)
         return false;
-    const bool long_k = !dense && d.n_groups <= 3 && d.K >= 1536;
-    return split_units(d) <= (long_k ? SPL_UNITS_LONG : SPL_UNITS);
+    const int64_t u = split_units(d), u4 = split_units4(d);
+    if (u <= SPL_UNITS)
+        return true;
+    if (dense)
+        return d.K >= 768 && u4 <= (d.K >= 1536 ? SPL_UNITS4 : 2560);
+    if (u4 <= SPL_UNITS4)
+        return true;
+    if (d.n_groups > 3 || d.K < 1536)
+        return false;
+    if ((d.M + BM - 1) / BM * d.n_groups <= num_cus())
+        return u4 <= 5000;
+    return u <= 10240 && n_tiles * 100 <= (int64_t)d.n_tile_rows * d.n_tile_cols * 60;
 }
 
 template <bool DENSE, int RT, int WV>
@@ -1320,14 +1341,14 @@ hipError_t launch_split(int dtype, bool gelu, const Args& a, const uint32_t* hal
         return launch_split_as<DENSE, 2, 8>(dtype, gelu, a, half_tiles, s);
     // (a long reduction gains more from half the X traffic per output: K = 3072, 600
     // units 4 x 4 18.3, 2 x 4 21.0; K = 768 8.2, 7.0)
-    if (u > 512 && u <= 1024 && a.d.K >= 1536)
+    if (u <= 1024 && a.d.K >= 1536)
         return launch_split_as<DENSE, 4, 4>(dtype, gelu, a, half_tiles, s);
     if (u <= 1024)
         return launch_split_as<DENSE, 2, 4>(dtype, gelu, a, half_tiles, s);
-    if (u <= 2048)
+    if (u <= SPL_UNITS)
         return launch_split_as<DENSE, 2, 2>(dtype, gelu, a, half_tiles, s);
     if constexpr (!DENSE) {
-        if (u > SPL_UNITS)
+        if (split_units4(a.d) > SPL_UNITS4)
             return launch_split_as<DENSE, 4, 1>(dtype, gelu, a, half_tiles, s);
     }
     return launch_split_as<DENSE, 4, 2>(dtype, gelu, a, half_tiles, s);
@@ -1509,9 +1530,9 @@ hipError_t launch_bsr_linear(const lpv_bsr* h, const LinearCall& c, hipStream_t 
     a.gdesc_host = h->gdesc_host;
     a.walk = h->walk;
     a.kh = h->b_c == 16;
-    if (use_split(a.d, false))
+    if (use_split(a.d, false, h->n_tiles))
         return launch_split<false>(h->dtype, c.gelu != 0, a, h->half_tiles, s);
-    if (use_xs(h, c.M, num_cus()))
+    if (use_xs(h, c.M, c.gelu != 0, num_cus()))
         return launch_xs_linear(h, c, num_cus(), s);
     return launch16<false>(h->dtype, c.gelu != 0, a, s);
 }
@@ -1525,7 +1546,7 @@ hipError_t launch_dense_linear(const void* W, int64_t ldw, int64_t N, int64_t K,
     Args a = base_args(c, N, K);
     a.W = (const char*)W;
     a.d.ldw = ldw;
-    if (use_split(a.d, true))
+    if (use_split(a.d, true, 0))
         return launch_split<true>(dtype, c.gelu != 0, a, nullptr, s);
     return launch16<true>(dtype, c.gelu != 0, a, s);
 }

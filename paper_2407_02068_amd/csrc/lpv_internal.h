@@ -107,7 +107,7 @@ hipError_t launch_dense_linear(const void* W, int64_t ldw, int64_t N, int64_t K,
                                const LinearCall& c, hipStream_t s);
 // stationary.hip: the product of a handle with row_vals, and whether it is the
 // faster one for M tokens
-bool use_xs(const lpv_bsr* h, int64_t M, int n_cus);
+bool use_xs(const lpv_bsr* h, int64_t M, bool gelu, int n_cus);
 hipError_t launch_xs_linear(const lpv_bsr* h, const LinearCall& c, int n_cus, hipStream_t s);
 
 // mask.hip

@@ -311,7 +311,7 @@ __global__ __launch_bounds__(XS_NT, 2) void k_linear16_xs(
 
 }  // namespace
 
-bool use_xs(const lpv_bsr* h, int64_t M, int n_cus)
+bool use_xs(const lpv_bsr* h, int64_t M, bool gelu, int n_cus)
 {
     if (!h->row_vals)
         return false;
@@ -324,6 +324,13 @@ bool use_xs(const lpv_bsr* h, int64_t M, int n_cus)
     // 3072: all kept 246 / 238, 70% 196 / 198, 50% 158 / 172).  With 16-wide block
     // columns k_linear16 skips the dropped halves of a tile; this kernel does not.
     const int64_t tiles = (int64_t)h->n_tile_rows * h->n_tile_cols;
+    // Steps: with few column tiles left to a group and whole groups k_linear16's items are
+    // short and this kernel's epilogues are the bound (768 x 768, 64 x 64 blocks, 45507
+    // tokens, 90%: 36.7 / 30.5; 1536 x 384, 19306: 21.2 / 17.5), unless the epilogue has the
+    // GELU, which k_linear16 does not overlap either (1024 x 512, 16611: 24.0 / 32.1), or a group
+    // is partial (1152 x 192, 31157, 50%: 24.4 / 40.8).
+    if (!gelu && h->n_steps < 10 * (int64_t)h->n_groups && h->n_tile_rows % GROUP_TILES == 0)
+        return false;
     return h->n_tiles * 100 <= tiles * (h->b_c == 16 ? 50 : 70);
 }
 

@@ -1,7 +1,10 @@
 """Helpers of the GPU tests: moving generated inputs to the device, reading
 results back, and the parity bar."""
+import re
+
 import numpy as np
 import torch
+from torch.profiler import ProfilerActivity, profile
 
 import oracle
 
@@ -53,3 +56,15 @@ def assert_close(y, r, dtype, what="", tile=(32, 32)):
     say("  %s rel err %.3e, per tile %.3e (bar %.0e)" % (what, err, terr, TOL[dtype]))
     assert err <= TOL[dtype], "%s: relative error %.3e above %.0e" % (what, err, TOL[dtype])
     assert terr <= TOL[dtype], "%s: per-tile relative error %.3e above %.0e" % (what, terr, TOL[dtype])
+
+
+def kernels(fn):
+    """The library's kernels that fn() launches, by name: so that a test of one kernel
+    can say that its sizes reach it."""
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        fn()
+        torch.cuda.synchronize()
+    names = {m.group(1) for e in p.key_averages() for m in [re.search(r"lpv::.*?::(k_\w+)", e.key)] if m}
+    assert names, "the profiler saw no kernel of the library"
+    return names

@@ -12,7 +12,7 @@ import torch
 
 import oracle
 import workloads as wl
-from gpu_util import TOL, TORCH, assert_close, bits, dev, f64, host, say
+from gpu_util import TOL, TORCH, assert_close, bits, dev, f64, host, kernels, say
 from paper_2407_02068_amd import lpv
 
 pytestmark = pytest.mark.gpu
@@ -123,6 +123,36 @@ def test_reduction_split_over_waves(M, N, K, b_r, b_c, dense):
         _, Y = run_bsr(w)
         r = ref(w)
     assert_close(f64(Y), r, w.dtype, w.name)
+
+
+@pytest.mark.parametrize("kernel,M,N,K,b_r,b_c,sparsity,gelu", [
+    ("k_linear16_split", 12608, 768, 3072, 32, 32, 50, False),   # long reduction, 4728 units
+    ("k_linear16", 18912, 768, 3072, 32, 32, 50, False),         # one round of items
+    ("k_linear16_split", 25216, 768, 3072, 64, 32, 70, False),   # two rounds
+    ("k_linear16", 25216, 768, 3072, 16, 16, 50, False),         # most tiles kept
+    ("k_linear16_split", 22064, 192, 192, 64, 64, 50, False),    # 2760 units in 4-row groups
+    ("k_linear16", 25039, 192, 192, 64, 64, 50, False),          # 3136
+    ("k_linear16_xs", 31157, 1152, 192, 32, 32, 50, False),      # a partial group
+    ("k_linear16", 45507, 768, 768, 64, 64, 90, False),          # few steps a group
+    ("k_linear16_xs", 45507, 768, 768, 64, 64, 90, True),
+    ("k_linear16", 45507, 768, 768, 32, 32, 20, False),          # most tiles kept
+    ("k_linear16_split", 1576, 2304, 768, None, None, 0, False), # dense, 1800 units
+    ("k_linear16", 3457, 1536, 384, None, None, 0, False),       # 2640, a short reduction
+    ("k_linear16_split", 1502, 4096, 2304, None, None, 0, False),
+])
+def test_route_16_bit(kernel, M, N, K, b_r, b_c, sparsity, gelu):
+    """The faster kernel by the measured lines of the dispatch."""
+    X = torch.zeros((M, K), dtype=torch.bfloat16, device="cuda")
+    W = torch.zeros((N, K), dtype=torch.bfloat16, device="cuda")
+    epi = "gelu" if gelu else None
+    if b_r is None:
+        call = lambda: lpv.dense_linear(W, X, None, epi=epi)
+    else:
+        w = wl.custom(46, 1, N, K, b_r, b_c, "bf16", "uniform", sparsity)
+        h = lpv.bsr_pack(W, dev(w.mask), b_r, b_c)
+        call = lambda: lpv.bsr_linear(h, X, None, epi=epi)
+    say("route", kernel, M, N, K, b_r, b_c, sparsity, gelu)
+    assert kernels(call) == {kernel}
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
