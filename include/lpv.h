@@ -263,8 +263,8 @@ lpv_status lpv_bsr_grad_w(const lpv_bsr* h, const void* G, int64_t ldg, const vo
  * lpv_bias_grad -- db[n] = sum over m of G[m][n] (N elements of type dt).
  * G device, M x N, row stride ldg >= N, 16-byte aligned, ldg a multiple of 16
  * bytes.  float32 sums over fixed token chunks added in order, one rounding.
- * Up to 4096 rows one launch without a workspace; above, allocates and frees a
- * stream-ordered one.  No host synchronisation.
+ * One launch without a workspace up to 4096 rows and 128 MiB of G; above, allocates
+ * and frees a stream-ordered one.  No host synchronisation.
  * M = 0 gives zeros.
  * Errors: INVALID_ARG, SHAPE, DTYPE, ALLOC, HIP.
  */

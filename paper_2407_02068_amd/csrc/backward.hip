@@ -151,11 +151,6 @@ __global__ __launch_bounds__(32 * BR_GROUPS) void k_bias_reduce(const float* __r
 // of columns (whole lines) and all rows; thread = 16 bytes of row g = tid / 8, g + 128, ...
 // (eight rows' loads in flight), then the wave's 8 row groups meet by shuffles and the 16
 // waves in LDS, in a fixed order.  Bound: latency of one pass, and what a CU can load.
-// Up to 4096 rows: 25 - 26 us per call for the chunks (two launches and a stream-ordered
-// allocation and free, host time), 8 - 11 us for this at 192 to 3072 columns.  Above, few
-// workgroups load too slowly: 6304 rows of 3072 in bf16 17 us, 12608 31 us, against 10
-// and 19 us of GPU time for the chunks.
-constexpr int64_t BIAS_DIRECT_ROWS = 4096;
 template <int DT>
 __global__ __launch_bounds__(1024) void k_bias_direct(const char* __restrict__ G, int64_t ldg,
                                                       int64_t M, int64_t N, char* __restrict__ db)
@@ -799,6 +794,20 @@ hipError_t scratch_err[MAX_DEVICES];
 
 }  // namespace
 
+// Whether k_bias_direct takes the call.  GPU us with G in memory, not in a cache, direct /
+// chunks: bf16, 768 columns, 2048 rows 6.9 / 13.5, 4096 10.7 / 13.8; 3072 columns, 2048 rows
+// 12.0 / 14.4, 4096 20.7 / 15.3; 16384 columns, 1024 rows 9.8 / 15.8; 65536 columns, 2048 rows
+// 68 / 60, 4096 136 / 101; fp32, 768 columns, 2048 rows 8.2 / 9.3, 4096 18.1 / 9.7.  Without an
+// allocation that decides; with one the chunks' call takes 20 us more of host time, which
+// the kernels hide only when they are long.
+static bool use_bias_direct(int64_t M, int64_t N, int dtype, bool alloc)
+{
+    const int64_t bytes = M * N * (dtype == LPV_F32 ? 4 : 2), MB = (int64_t)1 << 20;
+    if (M > 4096)
+        return false;
+    return bytes <= (alloc ? 128 * MB : M <= 2048 ? 32 * MB : 4 * MB);
+}
+
 // One launch without a workspace (k_bias_direct), in place of the chunks.
 static hipError_t launch_bias_direct(const void* G, int64_t ldg, int64_t M, int64_t N, int dtype,
                                      void* db, hipStream_t s)
@@ -820,7 +829,7 @@ static hipError_t launch_bias_direct(const void* G, int64_t ldg, int64_t M, int6
 hipError_t launch_bias_grad(const void* G, int64_t ldg, int64_t M, int64_t N, int dtype, void* db,
                             hipStream_t s)
 {
-    if (M <= BIAS_DIRECT_ROWS)
+    if (use_bias_direct(M, N, dtype, true))
         return launch_bias_direct(G, ldg, M, N, dtype, db, s);
     int64_t rows = 0;
     const int64_t n_chunks = bias_chunks(M, N, dtype == LPV_F32 ? 4 : 8, (int64_t)1 << 40, &rows);
@@ -836,7 +845,7 @@ hipError_t launch_bias_grad(const void* G, int64_t ldg, int64_t M, int64_t N, in
 hipError_t launch_bias_grad_noalloc(const void* G, int64_t ldg, int64_t M, int64_t N, int dtype,
                                     void* db, hipStream_t s)
 {
-    if (M <= BIAS_DIRECT_ROWS)
+    if (use_bias_direct(M, N, dtype, false))
         return launch_bias_direct(G, ldg, M, N, dtype, db, s);
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);

@@ -7,7 +7,7 @@ import torch
 
 import oracle
 import workloads as wl
-from gpu_util import TOL, assert_close, bits, dev, f64, host, say
+from gpu_util import TOL, TORCH, assert_close, bits, dev, f64, host, kernels, say
 from paper_2407_02068_amd import lpv
 
 pytestmark = pytest.mark.gpu
@@ -130,14 +130,34 @@ def test_backward_partial_group(dtype, N, sparsity):
 @pytest.mark.parametrize("M,N", [(1, 16), (127, 72), (129, 196), (1024, 33), (1025, 64), (4096, 100),
                                  (4097, 100)])
 def test_bias_grad_direct(M, N, dtype):
-    # one launch up to 4096 rows (128 row groups, 8 rows each at a time), chunks above;
-    # ragged columns, rows further apart than they are long
+    # one launch up to 4096 rows (128 row groups, 8 rows each at a time) of these few columns,
+    # chunks above; ragged columns, rows further apart than they are long
     G = wl.grad_output(121, 0, M, N, dtype)
     wide = torch.full((M, (N + 15) // 8 * 8), 1e4, dtype=dev(G, dtype).dtype, device="cuda")
     wide[:, :N] = dev(G, dtype)
     db = lpv.bias_grad(wide[:, :N])
     torch.cuda.synchronize()
     assert_close(f64(db), oracle.grad_bias(G, dtype), dtype, "bias grad %d x %d" % (M, N))
+
+
+@pytest.mark.parametrize("M,N,dtype,one,noalloc_one", [
+    (4096, 512, "bf16", True, True),
+    (4097, 64, "bf16", False, False),
+    (2048, 768, "f32", True, True),
+    (4096, 768, "f32", True, False),     # the loads of one workgroup a column block are the bound
+    (1024, 16384, "bf16", True, True),
+    (1025, 16384, "bf16", True, False),
+    (1025, 65536, "bf16", False, False), # and here all of them: 128 MiB
+])
+def test_bias_grad_route(M, N, dtype, one, noalloc_one):
+    G = torch.ones((M, N), dtype=TORCH[dtype], device="cuda")
+    db = torch.zeros(N, dtype=G.dtype, device="cuda")
+    say("bias grad route", M, N, dtype)
+    for f, direct in ((lpv.bias_grad, one), (lpv.bias_grad_noalloc, noalloc_one)):
+        db.zero_()
+        assert kernels(lambda: f(G, db)) == ({"k_bias_direct"} if direct else
+                                             {"k_bias_partial", "k_bias_reduce"})
+        assert torch.equal(db, torch.full_like(db, M))  # (rounded as the sum is)
 
 
 def test_backward_m0():
