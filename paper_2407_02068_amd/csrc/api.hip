@@ -111,7 +111,7 @@ void free_handle(lpv_bsr* h)
 {
     if (!h)
         return;
-    void* bufs[] = {h->meta, h->data, h->gradw_ws};
+    void* bufs[] = {h->meta, h->data[0], h->data[1], h->data[2], h->data[3], h->gradw_ws};
     for (void* p : bufs)
         if (p)
             (void)hipFree(p);
@@ -142,9 +142,7 @@ lpv_status pack_weight(lpv::PackArgs a, int64_t N, int64_t K, int dt, int32_t b_
     // The first buffer, int32 words: gdesc (16-byte entries) and the plan after it (one
     // copy to the host brings both), walk (8-byte entries), half_tiles, row_ptr,
     // group_order, step_ptr, group_tile0, row_tile0, row_mask and the steps.  The step
-    // and walk arrays are sized for every column of every group.  (Buffers under about
-    // 2 MB are cut from memory the runtime holds, 1 us; a larger one costs tens to hundreds
-    // of us to map and to free, so a handle has one of each.)
+    // and walk arrays are sized for every column of every group.
     const bool rows = mfma_path && K % (2 * lpv::TILE) == 0 && h->n_tile_cols <= lpv::XS_COLS &&
                       h->n_tile_rows <= lpv::XS_ROWS;
     const size_t ng = (size_t)h->n_groups, nc = (size_t)((h->n_tile_cols + 1) & ~1);
@@ -234,24 +232,41 @@ lpv_status pack_weight(lpv::PackArgs a, int64_t N, int64_t K, int dt, int32_t b_
         return fail(LPV_ERR_SHAPE, "%lld kept 32 x 32 tiles: at most 2^21 - 1 are supported", nt);
     }
 
-    // the second buffer: values, the tiles in operand order (and again by tile row), col_idx
-    const size_t b_val = (size_t)h->nnzb * b_r * b_c * es;  // (multiples of 512 bytes)
+    // values, the tiles in operand order (and again by tile row) and col_idx, put together
+    // where one allocation costs less than two (us to allocate and to free, by size:
+    // under 2 MiB 0.7 + 0.6, up to 4 MiB 11 + 12, up to 64 MiB 7 + 6, above 28 + 260)
     const size_t b_str = (size_t)h->n_tiles * lpv::TILE * lpv::TILE * es;
-    e = dmalloc(&h->data, b_val + b_str * (rows ? 2 : 1) + (size_t)h->nnzb * sizeof(int32_t));
-    if (e != hipSuccess) {
-        free_handle(h);
-        return e == hipErrorOutOfMemory ? fail(LPV_ERR_ALLOC, "device allocation failed")
-                                        : hip_fail(e, "hipMalloc");
+    const struct {
+        void** at;
+        size_t bytes;
+    } parts[4] = {{&h->values, (size_t)h->nnzb * b_r * b_c * es},
+                  {&h->stream_vals, b_str},
+                  {&h->row_vals, rows ? b_str : 0},
+                  {(void**)&h->col_idx, (size_t)h->nnzb * sizeof(int32_t)}};
+    constexpr size_t SMALL = (size_t)2 << 20, LARGE = (size_t)64 << 20;
+    size_t used[4] = {}, off[4];
+    int in[4];
+    for (int i = 0; i < 4; ++i) {
+        const size_t n = (parts[i].bytes + 511) / 512 * 512;  // (every part 512-byte aligned)
+        int k = 0;
+        while (used[k] && !(used[k] + n < SMALL ||
+                            (used[k] >= SMALL && n >= SMALL && used[k] + n <= LARGE)))
+            ++k;  // (ends at an empty one: at most a part in each before it)
+        in[i] = k;
+        off[i] = used[k];
+        used[k] += n;
     }
-    if (h->data) {
-        char* p = (char*)h->data;
-        h->values = p;
-        if (h->n_tiles > 0)
-            h->stream_vals = p + b_val;
-        if (rows && h->n_tiles > 0)
-            h->row_vals = p + b_val + b_str;
-        h->col_idx = (int32_t*)(p + b_val + b_str * (rows ? 2 : 1));
+    for (int k = 0; k < 4; ++k) {
+        e = dmalloc(&h->data[k], used[k]);
+        if (e != hipSuccess) {
+            free_handle(h);
+            return e == hipErrorOutOfMemory ? fail(LPV_ERR_ALLOC, "device allocation failed")
+                                            : hip_fail(e, "hipMalloc");
+        }
     }
+    for (int i = 0; i < 4; ++i)
+        if (parts[i].bytes)
+            *parts[i].at = (char*)h->data[in[i]] + off[i];
     e = lpv::launch_pack_fill(a, h, s);
     if (e == hipSuccess)
         e = hipStreamSynchronize(s);

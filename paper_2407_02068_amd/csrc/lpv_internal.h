@@ -35,7 +35,7 @@ struct lpv_bsr {
     int32_t device;
     void* meta;  // one allocation: the index arrays and the schedule (sizes known before the
                  // kept count is)
-    void* data;  // one allocation: values, stream_vals, row_vals, col_idx
+    void* data[4];  // values, stream_vals, row_vals and col_idx, in as few allocations as pay
     // canonical BSR
     int32_t* row_ptr;  // R + 1
     int32_t* col_idx;  // nnzb
@@ -60,7 +60,7 @@ struct lpv_bsr {
     // the same tiles by tile row, ascending columns (weights that fit XS_COLS x
     // XS_ROWS tiles, K a multiple of 64; NULL otherwise): row r's are row_tile0[r] .. row_tile0[r + 1],
     // bit c of row_mask[r] set for tile column c
-    void* row_vals;        // in the stream_vals allocation
+    void* row_vals;
     int32_t* row_tile0;    // n_tile_rows + 1
     uint32_t* row_mask;    // n_tile_rows
     // workspace of lpv_bsr_grad_w (per-chunk float32 partial sums of every

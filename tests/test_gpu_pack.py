@@ -8,7 +8,7 @@ import torch
 
 import oracle
 import workloads as wl
-from gpu_util import bits, dev, host, say
+from gpu_util import TOL, bits, dev, host, say
 from paper_2407_02068_amd import lpv
 
 pytestmark = pytest.mark.gpu
@@ -83,6 +83,29 @@ def test_pack_deit_shapes(kind):
     say("pack deit", w.name)
     h = _pack_and_compare(w.W, w.mask, w.dtype, w.b_r, w.b_c)
     check_schedule(h, w.mask, w.b_r, w.b_c, w.N, w.K)
+
+
+@pytest.mark.parametrize("N,K,b,dtype,keep", [
+    (1280, 576, 32, "bf16", 0.6),   # values and tiles together under 2 MiB, the row-major tiles not
+    (1536, 640, 32, "bf16", 0.9),   # all three under 2 MiB, no two together
+    (3072, 768, 32, "bf16", 0.9),   # three above, together
+    (8192, 3072, 64, "f16", 0.75),  # two above, more than 64 MiB together
+    (4096, 4096, 64, "f32", 1.0),   # 64 MiB of values, the column indices beside them
+])
+def test_pack_buffer_sizes(N, K, b, dtype, keep):
+    """The values and tile copies share allocations by their sizes; 14336 tokens for the
+    kernel that reads the row-major tiles."""
+    say("pack buffers", N, K, b, dtype, keep)
+    W, mask = _case(78, N, K, b, b, dtype, keep)
+    h = _pack_and_compare(W, mask, dtype, b, b)
+    if dtype != "f32":
+        check_schedule(h, mask, b, b, N, K)
+    Wu = lpv.bsr_unpack(h)
+    M = 14336 if K <= 768 else 64
+    X = torch.randn((M, K), device="cuda").to(Wu.dtype)
+    Y, r = lpv.bsr_linear(h, X).float(), X.float() @ Wu.float().t().contiguous()
+    # sums of K products of N(0, 1) in another order, and one rounding
+    assert (Y - r).abs().max() <= TOL[dtype] * r.abs().max()
 
 
 def check_schedule(h, mask, b_r, b_c, N, K):
