@@ -106,12 +106,14 @@ __global__ __launch_bounds__(SC_THREADS) void k_block_scores_lds(const char* __r
 // rank[b] = #{b' : score(b') > score(b), or equal and b' < b}: perm[rank[b]] = b
 // (perm, if given) and mask[b] = rank[b] < n_keep (mask, if given).  Scores are
 // non-negative, so their bit patterns order like their values.  Workgroup: RANK_B
-// blocks; thread t counts for block t % RANK_B the keys t / RANK_B, t / RANK_B +
-// RANK_PARTS, ... above it, and at or above it; only where another key is equal
-// does a second pass count the equal ones before it.  The keys come through LDS
+// blocks; thread t takes for block t % RANK_B the keys t / RANK_B, t / RANK_B +
+// RANK_PARTS, ... and counts those at or above it up to the block's own place, those
+// above it from there on: one compare a key, ties or not.  The keys come through LDS
 // (RANK_CHUNK at a time); integer counts, exact in any order.  Bound: the 64-bit
 // compares, so few blocks per workgroup and the whole chip (64 blocks per workgroup
-// kept 36 CUs busy with 2304 blocks: 12.6 us; this 5.4).
+// kept 36 CUs busy with 2304 blocks: 12.6 us; this 5.4).  The delta curve of 131072 blocks,
+// nearly all of it ranking, 2.89 ms, of 65536 0.78; counting equal keys in a pass of their
+// own took 3.31 and 0.88 without ties, 6.53 and 1.72 with them.
 constexpr int RANK_B = 8;
 constexpr int RANK_NT = 1024;
 constexpr int RANK_PARTS = RANK_NT / RANK_B;
@@ -125,62 +127,38 @@ __global__ __launch_bounds__(RANK_NT) void k_rank(const double* __restrict__ sco
 {
     __shared__ uint64_t s_keys[RANK_CHUNK];
     __shared__ int32_t s_cnt[RANK_NT / 64][RANK_B];
-    __shared__ int s_tie;
     const int tid = threadIdx.x, part = tid / RANK_B;
     const int64_t b = (int64_t)blockIdx.x * RANK_B + tid % RANK_B;
     const uint64_t* keys = (const uint64_t*)scores;
     const uint64_t key = keys[min(b, nb - 1)];
-    if (tid == 0)
-        s_tie = 0;
-    // the threads' counts of a block, added over the workgroup (for tid < RANK_B)
-    auto add_up = [&](int32_t v) {
-#pragma unroll
-        for (int o = RANK_B; o < 64; o <<= 1)
-            v += __shfl_xor(v, o, 64);
-        __syncthreads();
-        if ((tid & 63) < RANK_B)
-            s_cnt[tid >> 6][tid & 63] = v;
-        __syncthreads();
-        int32_t sum = 0;
-        if (tid < RANK_B)
-#pragma unroll
-            for (int j = 0; j < RANK_NT / 64; ++j)
-                sum += s_cnt[j][tid];
-        return sum;
-    };
-    auto stage = [&](int64_t c0) {  // keys c0 .. into LDS; how many
+    int32_t ahead = 0;
+    for (int64_t c0 = 0; c0 < nb; c0 += RANK_CHUNK) {
         const int n = (int)min((int64_t)RANK_CHUNK, nb - c0);
         __syncthreads();  // the chunk before is counted
         for (int i = tid; i < n; i += RANK_NT)
             s_keys[i] = keys[c0 + i];
         __syncthreads();
-        return n;
-    };
-    int32_t above = 0, least = 0;
-    for (int64_t c0 = 0; c0 < nb; c0 += RANK_CHUNK) {
-        const int n = stage(c0);
+        const int own = (int)min(max(b - c0, (int64_t)0), (int64_t)n);  // the block's place in the chunk
+        int i = part;
 #pragma unroll 4
-        for (int i = part; i < n; i += RANK_PARTS) {
-            const uint64_t k2 = s_keys[i];
-            above += k2 > key;
-            least += k2 >= key;
-        }
+        for (; i < own; i += RANK_PARTS)
+            ahead += s_keys[i] >= key;
+#pragma unroll 4
+        for (; i < n; i += RANK_PARTS)
+            ahead += s_keys[i] > key;
     }
-    int32_t rank = add_up(above);
-    const int32_t equal = add_up(least) - rank;  // the block itself and its ties
-    if (tid < RANK_B && b < nb && equal > 1)
-        s_tie = 1;
+    // the threads' counts of a block, added over the workgroup
+#pragma unroll
+    for (int o = RANK_B; o < 64; o <<= 1)
+        ahead += __shfl_xor(ahead, o, 64);
+    if ((tid & 63) < RANK_B)
+        s_cnt[tid >> 6][tid & 63] = ahead;
     __syncthreads();
-    if (s_tie) {  // (uniform)
-        int32_t before = 0;
-        for (int64_t c0 = 0; c0 < nb; c0 += RANK_CHUNK) {
-            const int n = stage(c0);
-            for (int i = part; i < n; i += RANK_PARTS)
-                before += s_keys[i] == key && c0 + i < b;
-        }
-        rank += add_up(before);
-    }
     if (tid < RANK_B && b < nb) {
+        int32_t rank = 0;
+#pragma unroll
+        for (int j = 0; j < RANK_NT / 64; ++j)
+            rank += s_cnt[j][tid];
         if (perm)
             perm[rank] = (int32_t)b;
         if (mask)

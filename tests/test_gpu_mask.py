@@ -108,3 +108,31 @@ def test_many_blocks_with_ties():
         check(Wi, "f32", 16, 16, p, what="12288 integer blocks")
     Gi = g.integers(-2, 3, (2048, 1536)).astype(np.float32)
     check(Wi.astype(np.float16), "f16", 16, 16, 50, Gi.astype(np.float16), what="12288 taylor")
+
+
+@pytest.mark.parametrize("N,K", [(16, 16 * 9), (2048, 1024), (128, 8208)])
+def test_ranking_with_ties_across_chunks(N, K):
+    # up to 8192 blocks every block is ranked, 4096 keys at a time and 8 blocks per
+    # workgroup: 9 blocks, two whole chunks, one chunk and 8 more
+    g = np.random.default_rng(68)
+    Wi = g.integers(-1, 2, (N, K)).astype(np.float32)
+    for p in (1, 50, 97):
+        check(Wi, "f32", 16, 16, p, what="integer blocks")
+    check(np.ones_like(Wi), "f32", 16, 16, 37, what="equal blocks")
+
+
+def test_ranking_of_equal_blocks_takes_no_longer():
+    # 32768 blocks, ranked for the delta curve: scores all different, and all equal
+    t = []
+    for W in (torch.randn((8192, 1024), device="cuda"), torch.ones((8192, 1024), device="cuda")):
+        ms = []
+        for _ in range(9):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            lpv.delta_curve(W, W, W[:0].reshape(0, 8192, 1024), 16, 16, 0.0, [0, 50, 100])
+            e1.record()
+            torch.cuda.synchronize()
+            ms.append(e0.elapsed_time(e1))
+        t.append(sorted(ms)[4])
+    say("ranking 32768 blocks: different %.3f ms, equal %.3f" % tuple(t))
+    assert t[1] <= 1.3 * t[0]
