@@ -245,10 +245,10 @@ __device__ inline void gw_dma_off(const char* base, uint32_t off, uint32_t m0)
 }
 
 // A workgroup takes one sub-tile of 16 VR x 16 VC elements of a kept block;
-// its 8 waves take runs of 16 tokens in turn, four v_mfma_f32_16x16x4_f32
+// its WV waves take runs of 16 tokens in turn, four v_mfma_f32_16x16x4_f32
 // (float32 products and sums) per run and 16 x 16 elements.  A run's pieces of
 // G and X rows (64 VR and 64 VC bytes) go by global->LDS DMA into the wave's
-// own ring of GWF_ST stages (no barrier: only the wave reads them); lane l
+// own ring of ST stages (no barrier: only the wave reads them); lane l
 // reads VR (VC) neighbouring columns of token 4 k + l / 16 for the k-th product,
 // at 256 VR consecutive bytes for the wave, and element e of them is row (column)
 // V (l % 16) + e of the sub-tile.  The waves' sums are added in wave order in
@@ -257,8 +257,10 @@ __device__ inline void gw_dma_off(const char* base, uint32_t off, uint32_t m0)
 // flight.  3152 tokens, 768 x 192, 288 16 x 16 blocks: 21 us (34 us with register
 // loads; 773 us with one thread per element, serial over the tokens), bound by
 // the 64-byte pieces of G and X that every block reads from L2.
-constexpr int GWF_WAVES = 8;
-constexpr int GWF_ST = 4;
+//
+// 8 waves of 4 stages, one to two workgroups per CU, and up to 64 tokens a wave and a
+// stage per run: 8 waves, most of them without a run, went round by round through many
+// blocks (1 token, 3052 16 x 64 blocks of 1792 x 3072: 47 us, this 11.6; 29421 16 x 16 blocks of 3072 x 3072 106 / 18; 64 tokens 48 / 16 and 114 / 54).
 typedef float gwf_x4 __attribute__((ext_vector_type(4)));
 typedef float gwf_x2 __attribute__((ext_vector_type(2)));
 
@@ -273,8 +275,8 @@ template <int V> __device__ inline void gwf_read(uint32_t addr, float* v)
     }
 }
 
-template <int VR, int VC>
-__global__ __launch_bounds__(64 * GWF_WAVES) void k_gradw_f32(int32_t b_r, int32_t b_c, int32_t R,
+template <int VR, int VC, int WV, int ST>
+__global__ __launch_bounds__(64 * WV) void k_gradw_f32(int32_t b_r, int32_t b_c, int32_t R,
                                                               const int32_t* __restrict__ row_ptr,
                                                               const int32_t* __restrict__ col_idx,
                                                               const float* __restrict__ G, int64_t ldg,
@@ -283,8 +285,8 @@ __global__ __launch_bounds__(64 * GWF_WAVES) void k_gradw_f32(int32_t b_r, int32
                                                               float* __restrict__ out)
 {
     constexpr int SB = (VR + VC) * 1024;  // bytes of a stage: 16 tokens of G, then of X
-    constexpr int RING = GWF_WAVES * GWF_ST * SB;
-    static_assert(GWF_WAVES * VR * VC * 1024 <= RING, "the waves' sums fit in the rings");
+    constexpr int RING = WV * ST * SB;
+    static_assert(WV * VR * VC * 1024 <= RING, "the waves' sums fit in the rings");
     __shared__ uint4 smem[RING / 16];
     // sub-tiles in BSR order, a contiguous run to each XCD (workgroup b runs on
     // XCD b % 8): an XCD's L2 then holds the G columns of its block rows
@@ -307,7 +309,7 @@ __global__ __launch_bounds__(64 * GWF_WAVES) void k_gradw_f32(int32_t b_r, int32
     // (16 rows of a leading dimension of at most 2^22)
     const int grow = lane / (4 * VR), xrow = lane / (4 * VC);
     const uint32_t gco = (lane % (4 * VR)) * 16, xco = (lane % (4 * VC)) * 16;
-    const uint32_t ring = lds_u32(smem) + (uint32_t)wave * (GWF_ST * SB);
+    const uint32_t ring = lds_u32(smem) + (uint32_t)wave * (ST * SB);
     auto dma = [&](int64_t run, int slot) {
         const int64_t m0 = run * 16;
         const int last = (int)min((int64_t)15, M - 1 - m0);  // rows past M repeat the last
@@ -324,13 +326,13 @@ __global__ __launch_bounds__(64 * GWF_WAVES) void k_gradw_f32(int32_t b_r, int32
     };
     gwf_x4 acc[VR][VC] = {};
     const int64_t runs = (M + 15) / 16;
-    const int64_t n = runs > wave ? (runs - wave + GWF_WAVES - 1) / GWF_WAVES : 0;  // this wave's
-    for (int k = 0; k < GWF_ST && k < n; ++k)
-        dma(wave + (int64_t)k * GWF_WAVES, k);
+    const int64_t n = runs > wave ? (runs - wave + WV - 1) / WV : 0;  // this wave's
+    for (int k = 0; k < ST && k < n; ++k)
+        dma(wave + (int64_t)k * WV, k);
     int slot = 0;
     for (int64_t k = 0; k < n; ++k) {
-        if (k + GWF_ST <= n)
-            asm volatile("s_waitcnt vmcnt(%0)" ::"i"((GWF_ST - 1) * (VR + VC)) : "memory");
+        if (k + ST <= n)
+            asm volatile("s_waitcnt vmcnt(%0)" ::"i"((ST - 1) * (VR + VC)) : "memory");
         else
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         const uint32_t at = ring + (uint32_t)slot * SB;
@@ -341,10 +343,10 @@ __global__ __launch_bounds__(64 * GWF_WAVES) void k_gradw_f32(int32_t b_r, int32
             gwf_read<VC>(at + VR * 1024 + (4 * e + q) * (64 * VC) + l16 * (4 * VC), x[e]);
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the stage may be filled again
-        if (k + GWF_ST < n)
-            dma(wave + (k + GWF_ST) * GWF_WAVES, slot);
-        slot = (slot + 1) % GWF_ST;
-        const int64_t m0 = (wave + k * GWF_WAVES) * 16;
+        if (k + ST < n)
+            dma(wave + (k + ST) * WV, slot);
+        slot = (slot + 1) % ST;
+        const int64_t m0 = (wave + k * WV) * 16;
         if (m0 + 16 > M) {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
@@ -374,11 +376,11 @@ __global__ __launch_bounds__(64 * GWF_WAVES) void k_gradw_f32(int32_t b_r, int32
     __syncthreads();
     // product (a, b): lane l, register i is row VR (4 (l / 16) + i) + a, column
     // VC (l % 16) + b of the sub-tile
-    for (int e = threadIdx.x; e < VR * VC * 64; e += 64 * GWF_WAVES) {
+    for (int e = threadIdx.x; e < VR * VC * 64; e += 64 * WV) {
         const int ab = e >> 6, ln = e & 63;
         gwf_x4 s = s_sum[e];
 #pragma unroll
-        for (int w = 1; w < GWF_WAVES; ++w)
+        for (int w = 1; w < WV; ++w)
             s += s_sum[w * VR * VC * 64 + e];
         const int j = j0 + VC * (ln & 15) + ab % VC;
 #pragma unroll
@@ -903,11 +905,23 @@ hipError_t launch_grad_w(const lpv_bsr* h, const GradWCall& c, hipStream_t s)
         const int vr = wide && h->b_r >= 32 ? 2 : 1, vc = wide && h->b_c >= 32 ? 2 : 1;
         const int64_t tiles = total / (256 * vr * vc);
         const Grid2 g = grid_of((tiles + 7) / 8 * 8);  // (up to 2^24 sub-tiles)
-        const dim3 grid(g.x, g.y), block(64 * GWF_WAVES);
-#define LPV_GWF(VR_, VC_)                                                                          \
-    hipLaunchKernelGGL((k_gradw_f32<VR_, VC_>), grid, block, 0, s, h->b_r, h->b_c, h->R,           \
-                       (const int32_t*)h->row_ptr, (const int32_t*)h->col_idx, (const float*)c.G,  \
-                       c.ldg, (const float*)c.X, c.ldx, c.M, tiles, (float*)c.dW)
+        const dim3 grid(g.x, g.y);
+        // (a wave per run of 16 tokens: the sums and their order are those of 8 waves)
+#define LPV_GWF4(VR_, VC_, WV_, ST_)                                                               \
+    hipLaunchKernelGGL((k_gradw_f32<VR_, VC_, WV_, ST_>), grid, dim3(64 * WV_), 0, s, h->b_r,      \
+                       h->b_c, h->R, (const int32_t*)h->row_ptr, (const int32_t*)h->col_idx,       \
+                       (const float*)c.G, c.ldg, (const float*)c.X, c.ldx, c.M, tiles, (float*)c.dW)
+#define LPV_GWF(VR_, VC_)                \
+    do {                                 \
+        if (c.M <= 16)                   \
+            LPV_GWF4(VR_, VC_, 1, 1);    \
+        else if (c.M <= 32)              \
+            LPV_GWF4(VR_, VC_, 2, 1);    \
+        else if (c.M <= 64)              \
+            LPV_GWF4(VR_, VC_, 4, 1);    \
+        else                             \
+            LPV_GWF4(VR_, VC_, 8, 4);    \
+    } while (0)
         if (vr == 2 && vc == 2)
             LPV_GWF(2, 2);
         else if (vr == 2)
@@ -917,6 +931,7 @@ hipError_t launch_grad_w(const lpv_bsr* h, const GradWCall& c, hipStream_t s)
         else
             LPV_GWF(1, 1);
 #undef LPV_GWF
+#undef LPV_GWF4
         return hipGetLastError();
     }
     GradWDims d = {};

@@ -58,13 +58,14 @@ def assert_close(y, r, dtype, what="", tile=(32, 32)):
     assert terr <= TOL[dtype], "%s: per-tile relative error %.3e above %.0e" % (what, terr, TOL[dtype])
 
 
-def kernels(fn):
-    """The library's kernels that fn() launches, by name: so that a test of one kernel
-    can say that its sizes reach it."""
+def kernels(fn, args=False):
+    """The library's kernels that fn() launches, by name (args: with their template
+    arguments): so that a test of one kernel can say that its sizes reach it."""
     torch.cuda.synchronize()
     with profile(activities=[ProfilerActivity.CUDA]) as p:
         fn()
         torch.cuda.synchronize()
-    names = {m.group(1) for e in p.key_averages() for m in [re.search(r"lpv::.*?::(k_\w+)", e.key)] if m}
+    pattern = r"lpv::.*?::(k_\w+%s)" % ("(?:<[^>]*>)?" if args else "")
+    names = {m.group(1) for e in p.key_averages() for m in [re.search(pattern, e.key)] if m}
     assert names, "the profiler saw no kernel of the library"
     return names

@@ -100,6 +100,23 @@ def test_backward_fp32_tiles(M, N, K, b_r, b_c):
     check_all(w, G, "fp32 tiles")
 
 
+@pytest.mark.parametrize("M,waves", [(1, 1), (16, 1), (17, 2), (32, 2), (33, 4), (64, 4), (65, 8)])
+@pytest.mark.parametrize("b_r,b_c,vr,vc", [(16, 16, 1, 1), (32, 32, 2, 2)])
+def test_backward_fp32_few_tokens(M, waves, b_r, b_c, vr, vc):
+    # a wave per run of 16 tokens up to 64, 8 waves above; integers, so that every sum is exact
+    w, _ = case(M, 512, 512, b_r, b_c, "f32", "all", cfg=97)
+    h = lpv.bsr_pack(dev(w.W, "f32"), dev(w.mask), b_r, b_c)
+    G = torch.randint(-8, 9, (M, 512), device="cuda").float()
+    X = torch.randint(-8, 9, (M, 512), device="cuda").float()
+    say("fp32 few tokens", M, b_r, b_c)
+    dW = lpv.grad_w(h, G, X)
+    ref = (G.double().t().contiguous() @ X.double()).reshape(512 // b_r, b_r, 512 // b_c, b_c)
+    assert torch.equal(dW.double(), ref.permute(0, 2, 1, 3).reshape(dW.shape))
+    vr, vc = (vr, vc) if dW.numel() // 1024 >= 256 else (1, 1)
+    assert kernels(lambda: lpv.grad_w(h, G, X, out=dW), args=True) == {
+        "k_gradw_f32<%d, %d, %d, %d>" % (vr, vc, waves, 4 if waves == 8 else 1)}
+
+
 @pytest.mark.parametrize("N,K", [(16384, 16400), (65536, 32768)])
 def test_backward_fp32_many_blocks(N, K):
     # more 16 x 16 sub-tiles than a row of the grid (2^20), and as many (2^23, 8 GB of
