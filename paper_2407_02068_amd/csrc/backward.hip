@@ -260,7 +260,8 @@ __device__ inline void gw_dma_off(const char* base, uint32_t off, uint32_t m0)
 //
 // 8 waves of 4 stages, one to two workgroups per CU, and up to 64 tokens a wave and a
 // stage per run: 8 waves, most of them without a run, went round by round through many
-// blocks (1 token, 3052 16 x 64 blocks of 1792 x 3072: 47 us, this 11.6; 29421 16 x 16 blocks of 3072 x 3072 106 / 18; 64 tokens 48 / 16 and 114 / 54).
+// blocks (1 token, 3052 16 x 64 blocks of 1792 x 3072: 47 us, this 11.6; 29421 16 x 16
+// blocks of 3072 x 3072 102 / 17; 64 tokens 48 / 15 and 113 / 51).
 typedef float gwf_x4 __attribute__((ext_vector_type(4)));
 typedef float gwf_x2 __attribute__((ext_vector_type(2)));
 
@@ -277,26 +278,26 @@ template <int V> __device__ inline void gwf_read(uint32_t addr, float* v)
 
 template <int VR, int VC, int WV, int ST>
 __global__ __launch_bounds__(64 * WV) void k_gradw_f32(int32_t b_r, int32_t b_c, int32_t R,
-                                                              const int32_t* __restrict__ row_ptr,
-                                                              const int32_t* __restrict__ col_idx,
-                                                              const float* __restrict__ G, int64_t ldg,
-                                                              const float* __restrict__ X, int64_t ldx,
-                                                              int64_t M, int64_t tiles,
-                                                              float* __restrict__ out)
+                                                       const int32_t* __restrict__ row_ptr,
+                                                       const int32_t* __restrict__ col_idx,
+                                                       const float* __restrict__ G, int64_t ldg,
+                                                       const float* __restrict__ X, int64_t ldx,
+                                                       int64_t M, int32_t tiles,
+                                                       float* __restrict__ out)
 {
     constexpr int SB = (VR + VC) * 1024;  // bytes of a stage: 16 tokens of G, then of X
     constexpr int RING = WV * ST * SB;
     static_assert(WV * VR * VC * 1024 <= RING, "the waves' sums fit in the rings");
     __shared__ uint4 smem[RING / 16];
     // sub-tiles in BSR order, a contiguous run to each XCD (workgroup b runs on
-    // XCD b % 8): an XCD's L2 then holds the G columns of its block rows
+    // XCD b % 8): an XCD's L2 then holds the G columns of its block rows.  (Numbers of at
+    // most 2^24 + 2^20; in 64 bits 3% slower: 29421 sub-tiles, 100 tokens 137 us, 125)
     const int scsh = __builtin_ctz(b_c / (16 * VC)), subsh = __builtin_ctz(b_r / (16 * VR)) + scsh;
-    const int64_t id = (int64_t)blockIdx.y * gridDim.x + blockIdx.x, per_xcd = (tiles + 7) / 8;
-    const int64_t item = (id & 7) * per_xcd + (id >> 3);
-    if (id >= 8 * per_xcd || item >= tiles)
+    const int id = (int)(blockIdx.y * gridDim.x + blockIdx.x), per_xcd = (tiles + 7) / 8;
+    const int item = (id & 7) * per_xcd + (id >> 3);
+    if ((id >> 3) >= per_xcd || item >= tiles)
         return;  // (the whole workgroup)
-    const int64_t p = item >> subsh;
-    const int sub = (int)(item - (p << subsh));
+    const int p = item >> subsh, sub = item - (p << subsh);
     const int i0 = (sub >> scsh) * (16 * VR);              // in the block
     const int j0 = (sub & ((1 << scsh) - 1)) * (16 * VC);
     const int r = block_row(row_ptr, R, p), c = col_idx[p];
@@ -386,7 +387,7 @@ __global__ __launch_bounds__(64 * WV) void k_gradw_f32(int32_t b_r, int32_t b_c,
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int row = i0 + VR * (4 * (ln >> 4) + i) + ab / VC;
-            out[(p * b_r + row) * b_c + j] = s[i];
+            out[((int64_t)p * b_r + row) * b_c + j] = s[i];
         }
     }
 }
@@ -910,7 +911,7 @@ hipError_t launch_grad_w(const lpv_bsr* h, const GradWCall& c, hipStream_t s)
 #define LPV_GWF4(VR_, VC_, WV_, ST_)                                                               \
     hipLaunchKernelGGL((k_gradw_f32<VR_, VC_, WV_, ST_>), grid, dim3(64 * WV_), 0, s, h->b_r,      \
                        h->b_c, h->R, (const int32_t*)h->row_ptr, (const int32_t*)h->col_idx,       \
-                       (const float*)c.G, c.ldg, (const float*)c.X, c.ldx, c.M, tiles, (float*)c.dW)
+                       (const float*)c.G, c.ldg, (const float*)c.X, c.ldx, c.M, (int32_t)tiles, (float*)c.dW)
 #define LPV_GWF(VR_, VC_)                \
     do {                                 \
         if (c.M <= 16)                   \
