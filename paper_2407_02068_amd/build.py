@@ -34,7 +34,7 @@ BUILD_DIR = os.path.join(HERE, "_build")
 # Kernels whose LDS ring counts every vector-memory instruction a wave issues
 # (vmcnt): a register spill to scratch would add uncounted ones, so any
 # scratch use there fails the build.
-NO_SCRATCH = ("k_linear16", "k_linear_f32", "k_gradw_f32", "k_linear16_xs")
+NO_SCRATCH = ("k_linear16", "k_linear_f32", "k_gradw_f32")
 
 
 def check_resources(remarks):

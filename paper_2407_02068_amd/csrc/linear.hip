@@ -804,7 +804,7 @@ __global__ __launch_bounds__(NT, 1) void k_linear16(
 // k_linear16's 256 x 256 items leave most of the chip idle when there are
 // fewer of them than CUs, and a lone item still takes a barrier and a DMA round
 // trip per pair of columns.  Bound: L2 -> LDS traffic (a step moves 8 KB of X and
-// 4 KB per kept row pair for 16 products per row) and the round trips left.
+// 4 KB per kept tile row for its 8 products) and the round trips left.
 // 197 tokens, 768 -> 3072, 50%, GELU: 6.0 us of GPU time (25.6 with
 // k_linear16); 1576 tokens, 3072 -> 768: 21 us (54).
 struct SplitDims {

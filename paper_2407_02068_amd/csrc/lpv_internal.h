@@ -123,7 +123,6 @@ struct MaskCall {
     double* scores;
 };
 hipError_t launch_mask_topk(const MaskCall& m, hipStream_t s);
-hipError_t launch_block_scores(const MaskCall& m, hipStream_t s);  // scores only
 // Ranks by (-score, index): perm[rank] = block and / or mask[block] = rank < n_keep.
 hipError_t launch_rank(const double* scores, int64_t nb, int64_t n_keep, int32_t* perm,
                        uint8_t* mask, hipStream_t s);

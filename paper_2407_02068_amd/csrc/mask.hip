@@ -32,11 +32,10 @@ template <int DT> __device__ inline double load_f64(const char* base, int64_t id
     return (double)(float)__builtin_bit_cast(_Float16, bits);
 }
 
-// One thread per block (r, c) = blockIdx.x * 256 + threadIdx.x (row-major).
-// VEC: the block's rows are read 16 bytes at a time (W and G 16-byte aligned,
-// row strides multiples of 16 bytes); the elements are still added one after
-// the other in row-major order, so the score is the same bit for bit.
-template <int DT, bool TAYLOR, bool VEC>
+// One thread per block (r, c) = blockIdx.x * 256 + threadIdx.x (row-major), element by
+// element: for weights and gradients that 16-byte loads cannot read (base or row stride
+// not a multiple of 16 bytes).
+template <int DT, bool TAYLOR>
 __global__ __launch_bounds__(256) void k_block_scores(const char* __restrict__ W, int64_t ldw,
                                                       const char* __restrict__ G, int64_t ldg,
                                                       int64_t R, int64_t C, int32_t b_r,
@@ -50,33 +49,14 @@ __global__ __launch_bounds__(256) void k_block_scores(const char* __restrict__ W
     double s = 0.0;
     for (int32_t a = 0; a < b_r; ++a) {
         const int64_t n = r * b_r + a;
-        if (VEC) {
-            for (int32_t b = 0; b < b_c; b += 8) {
-                const int64_t k = c * b_c + b;
-                double w[8], g[8];
-                load8_f64<DT>(W, n * ldw + k, w);
-                if (TAYLOR)
-                    load8_f64<DT>(G, n * ldg + k, g);
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    if (TAYLOR) {
-                        const double p = w[j] * g[j];
-                        s = s + (p < 0.0 ? -p : p);
-                    } else {
-                        s = s + w[j] * w[j];
-                    }
-                }
-            }
-        } else {
-            for (int32_t b = 0; b < b_c; ++b) {
-                const int64_t k = c * b_c + b;
-                const double w = load_f64<DT>(W, n * ldw + k);
-                if (TAYLOR) {
-                    const double p = w * load_f64<DT>(G, n * ldg + k);
-                    s = s + (p < 0.0 ? -p : p);
-                } else {
-                    s = s + w * w;
-                }
+        for (int32_t b = 0; b < b_c; ++b) {
+            const int64_t k = c * b_c + b;
+            const double w = load_f64<DT>(W, n * ldw + k);
+            if (TAYLOR) {
+                const double p = w * load_f64<DT>(G, n * ldg + k);
+                s = s + (p < 0.0 ? -p : p);
+            } else {
+                s = s + w * w;
             }
         }
     }
@@ -176,10 +156,8 @@ __device__ inline uint64_t key_of(double v) { return (uint64_t)__double_as_longl
 // bytes found so far, an LDS histogram of the next byte gives the byte of T
 // and how many keys above it drop out.  Then every key > T is kept, and of the
 // keys == T the (n_keep - #keys > T) lowest indices (wave ballots give each
-// tie its rank in index order).  Up to SEL_REG keys per thread stay in
-// registers; more are read again from global memory in every pass.
-constexpr int SEL_REG = 8;
-
+// tie its rank in index order).  The keys (more than RANK_MAX) are read from global
+// memory in every pass.
 __global__ __launch_bounds__(SEL_THREADS) void k_mask_topk(const double* __restrict__ scores,
                                                            int64_t n, int64_t n_keep,
                                                            uint8_t* __restrict__ mask)
@@ -193,13 +171,6 @@ __global__ __launch_bounds__(SEL_THREADS) void k_mask_topk(const double* __restr
             mask[i] = 0;
         return;
     }
-    const bool in_reg = n <= (int64_t)SEL_REG * SEL_THREADS;
-    uint64_t kr[SEL_REG];
-#pragma unroll
-    for (int q = 0; q < SEL_REG; ++q) {
-        const int64_t i = (int64_t)q * SEL_THREADS + tid;
-        kr[q] = in_reg && i < n ? key_of(scores[i]) : 0;
-    }
     uint64_t prefix = 0, pmask = 0;
     int64_t remaining = n_keep;  // rank of T among the keys matching the prefix
     for (int byte = 7; byte >= 0; --byte) {
@@ -207,19 +178,10 @@ __global__ __launch_bounds__(SEL_THREADS) void k_mask_topk(const double* __restr
         for (int i = tid; i < 256; i += SEL_THREADS)
             s_hist[i] = 0;
         __syncthreads();
-        if (in_reg) {
-#pragma unroll
-            for (int q = 0; q < SEL_REG; ++q) {
-                const int64_t i = (int64_t)q * SEL_THREADS + tid;
-                if (i < n && (kr[q] & pmask) == prefix)
-                    atomicAdd(&s_hist[(kr[q] >> sh) & 255], 1u);
-            }
-        } else {
-            for (int64_t i = tid; i < n; i += SEL_THREADS) {
-                const uint64_t k = key_of(scores[i]);
-                if ((k & pmask) == prefix)
-                    atomicAdd(&s_hist[(k >> sh) & 255], 1u);
-            }
+        for (int64_t i = tid; i < n; i += SEL_THREADS) {
+            const uint64_t k = key_of(scores[i]);
+            if ((k & pmask) == prefix)
+                atomicAdd(&s_hist[(k >> sh) & 255], 1u);
         }
         __syncthreads();
         if (wave == 0) {
@@ -265,8 +227,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_mask_topk(const double* __restr
     int64_t taken = 0;
     for (int64_t base = 0; base < n; base += SEL_THREADS) {
         const int64_t i = base + tid;
-        const int q = (int)(base / SEL_THREADS);
-        const uint64_t k = i < n ? (in_reg && q < SEL_REG ? kr[q] : key_of(scores[i])) : 0;
+        const uint64_t k = i < n ? key_of(scores[i]) : 0;
         const bool tie = i < n && k == T;
         const uint64_t bal = __ballot(tie);
         const int64_t before_in_wave = __popcll(bal & (((uint64_t)1 << lane) - 1));
@@ -285,8 +246,6 @@ __global__ __launch_bounds__(SEL_THREADS) void k_mask_topk(const double* __restr
         __syncthreads();  // s_part is rewritten by the next chunk
     }
 }
-
-}  // namespace
 
 hipError_t launch_block_scores(const MaskCall& m, hipStream_t s)
 {
@@ -325,19 +284,15 @@ hipError_t launch_block_scores(const MaskCall& m, hipStream_t s)
     }
     if (nb > 0) {
         const dim3 grid((unsigned)((nb + 255) / 256)), block(256);
-#define LPV_SCORES(DT_, TY_, V_)                                                                   \
-    hipLaunchKernelGGL((k_block_scores<DT_, TY_, V_>), grid, block, 0, s, (const char*)m.W, m.ldw, \
+#define LPV_SCORES(DT_, TY_)                                                                       \
+    hipLaunchKernelGGL((k_block_scores<DT_, TY_>), grid, block, 0, s, (const char*)m.W, m.ldw,     \
                        (const char*)m.G, m.ldg, R, C, m.b_r, m.b_c, m.scores)
-#define LPV_SCORES_DT(DT_)                   \
-    do {                                     \
-        if (m.G && vec)                      \
-            LPV_SCORES(DT_, true, true);     \
-        else if (m.G)                        \
-            LPV_SCORES(DT_, true, false);    \
-        else if (vec)                        \
-            LPV_SCORES(DT_, false, true);    \
-        else                                 \
-            LPV_SCORES(DT_, false, false);   \
+#define LPV_SCORES_DT(DT_)             \
+    do {                               \
+        if (m.G)                       \
+            LPV_SCORES(DT_, true);     \
+        else                           \
+            LPV_SCORES(DT_, false);    \
     } while (0)
         if (m.dtype == LPV_BF16)
             LPV_SCORES_DT(LPV_BF16);
@@ -350,6 +305,8 @@ hipError_t launch_block_scores(const MaskCall& m, hipStream_t s)
     }
     return hipGetLastError();
 }
+
+}  // namespace
 
 hipError_t launch_rank(const double* scores, int64_t nb, int64_t n_keep, int32_t* perm,
                        uint8_t* mask, hipStream_t s)

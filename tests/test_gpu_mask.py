@@ -100,7 +100,7 @@ def test_unaligned_weight_rows():
 
 
 def test_many_blocks_with_ties():
-    # 12288 blocks (more keys than the selection keeps in registers) of small
+    # 12288 blocks (more than the 8192 that are ranked: the radix selection) of small
     # integers, so many block scores are equal: ties still go to the lower index
     g = np.random.default_rng(67)
     Wi = g.integers(-2, 3, (2048, 1536)).astype(np.float32)
