@@ -83,8 +83,8 @@ def test_fp32_tiles(M, N, K, b_r, b_c):
 
 @pytest.mark.parametrize("M", [2**26 + 24, 2**30 - 256])
 def test_fp32_many_tokens(M):
-    # more token tiles (64 tokens) than a row of the grid (2^20), and as many as bring one grid
-    # dimension to its limit once rounded up to the 8 XCDs (128 GiB of X and Y).  The
+    # more token tiles (64 tokens) than one launch takes (2^20), and as many as would bring one
+    # grid dimension to its limit once rounded up to the 8 XCDs (128 GiB of X and Y).  The
     # identity as weight: Y is X
     if torch.cuda.mem_get_info()[0] < 150 * M:
         pytest.skip("needs %d GB of free device memory" % (150 * M // 10**9))
