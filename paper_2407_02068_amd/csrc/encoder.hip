@@ -164,10 +164,10 @@ __global__ __launch_bounds__(NT) void k_attention(const uint16_t* __restrict__ q
     using E = Elem<DT>;
     using F = typename E::frag;
     extern __shared__ uint4 att_lds[];  // K rows, then V rows
-    const int64_t id = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-    if (id >= heads)
+    const uint32_t id = blockIdx.y * gridDim.x + blockIdx.x;  // (below 2^31 + 2^20)
+    if (id >= (uint32_t)heads)
         return;  // (the whole workgroup)
-    const int seq = (int)id / H, h = (int)id - seq * H;
+    const int seq = (int)(id / (uint32_t)H), h = (int)id - seq * H;
     const int n_kt = (T + 31) / 32, Tp = 32 * n_kt;
     const int64_t ld = 3 * (int64_t)H * ATT_HD, ldo = (int64_t)H * ATT_HD;
     const uint16_t* base = qkv + (int64_t)seq * T * ld;
