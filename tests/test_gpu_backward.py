@@ -87,7 +87,7 @@ def test_backward_fp32():
     check_all(w, G, "fp32 tiny")
 
 
-@pytest.mark.parametrize("M", [1, 5, 255, 256, 259])
+@pytest.mark.parametrize("M", [1, 5, 128, 129, 255, 256, 259, 385, 512, 513, 1025, 1163])
 @pytest.mark.parametrize("N,K,b_r,b_c", [
     (64, 96, 32, 16),      # few blocks: 16 x 16 sub-tiles
     (1024, 1024, 64, 32),  # 32 x 32 sub-tiles
@@ -95,7 +95,8 @@ def test_backward_fp32():
     (512, 512, 32, 16),    # 32 x 16
 ])
 def test_backward_fp32_tiles(M, N, K, b_r, b_c):
-    # token groups of 4, batches of 8 groups per wave, 8 waves: 256 tokens a batch
+    # runs of 16 tokens dealt to 8 waves, 4 stages a wave: up to 128 tokens a run each, from
+    # 385 on a wave waits for part of its ring, from 513 on it fills stages again
     w, G = case(M, N, K, b_r, b_c, "f32", "all", cfg=97)
     check_all(w, G, "fp32 tiles")
 
@@ -137,7 +138,8 @@ def test_backward_fp32_many_blocks(N, K):
 @pytest.mark.parametrize("N,sparsity", [(384, 0), (384, 50), (192, 30), (512, 60)])
 def test_backward_partial_group(dtype, N, sparsity):
     # the last group of 8 tile rows is partial (or whole) and a window's row 3
-    # keeps its column 7: rows past the weight must neither be computed nor written
+    # keeps its column 7, the sign bit of the row masks' lower word: the values (rows past the
+    # weight would be written behind the handle's workspace, which no test sees)
     w, G = case(1616, N, 768, 32, 32, dtype, "uniform", sparsity, cfg=98)
     w.mask[3::8, 7::8] = 1
     check_all(w, G, "partial group")

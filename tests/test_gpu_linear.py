@@ -286,12 +286,43 @@ def test_deterministic_and_token_permutation():
     assert torch.equal(Yp.view(torch.int16), Y1[perm].view(torch.int16))
 
 
+@pytest.mark.parametrize("kernel,M,N,K,b_r,b_c,dtype,sparsity", [
+    ("k_linear16_xs", 42 * 256 - 31, 1552, 192, 16, 32, "bf16", 60),
+    ("k_linear16_xs", 22 * 256 + 33, 3072, 448, 64, 64, "f16", 60),
+    ("k_linear16", 42 * 256 - 31, 1552, 192, 16, 32, "bf16", 20),
+    ("k_linear16", 42 * 256 - 31, 1552, 192, 16, 16, "f16", 40),  # tiles walked by halves
+    ("k_linear16_split", 1217, 2512, 192, 16, 32, "f16", 40),
+])
+def test_guard_bands_of_each_kernel(kernel, M, N, K, b_r, b_c, dtype, sparsity):
+    """ldx > K, with NaN in the columns around X and the rows before and after it; ldy > N,
+    canaries all around Y; ragged tokens and outputs.  The 16-bit kernels of larger
+    products, each by name."""
+    w = wl.custom(68, M, N, K, b_r, b_c, dtype, "uniform", sparsity)
+    tt = TORCH[dtype]
+    big = torch.full((M + 2, 3 * K), float("nan"), dtype=tt, device="cuda")
+    big[1:M + 1, K:2 * K] = dev(w.X, dtype)
+    Xv = big[1:M + 1, K:2 * K]
+    canary = torch.full((M + 2, N + 128), -7.0, dtype=tt, device="cuda")
+    Yv = canary[1:M + 1, 64:64 + N]
+    h = lpv.bsr_pack(dev(w.W, dtype), dev(w.mask), b_r, b_c)
+    b = dev(w.bias, dtype)
+    say("guard bands", kernel, M, N, K, b_r, b_c, dtype)
+    assert kernels(lambda: lpv.bsr_linear(h, Xv, b, Y=Yv)) == {kernel}
+    rows = _sampled_rows(M, n=96, seed=4)
+    assert_close(f64(Yv[torch.from_numpy(rows).cuda()]), ref(w, w.X[rows]), dtype, w.name)
+    # (every element, against a call on plain buffers)
+    assert torch.equal(Yv, lpv.bsr_linear(h, dev(w.X, dtype), b))
+    canary[1:M + 1, 64:64 + N] = -7.0
+    assert torch.all(canary == -7.0)
+
+
 @pytest.mark.parametrize("dtype,b_c,K", [("bf16", 32, 192), ("bf16", 16, 176), ("f32", 16, 192)])
 def test_strided_views_and_guard_bands(dtype, b_c, K):
     """X read through a column slice of a wider buffer (ldx > K); Y written
-    into the middle of a padded buffer (ldy > N) whose canaries must survive.
-    Also with 16-wide block columns and a 16-column reduction tail (the
-    half-tile walk and the zero line in place of X past K)."""
+    into the middle of a padded buffer (ldy > N) whose canaries must survive:
+    few tokens (the reduction split over waves), fp32, and 16-wide block columns with a
+    16-column reduction tail (the half-tile walk and the zero line in place of X past
+    K)."""
     w = wl.custom(65, 197, 256, K, 32, b_c, dtype, "uniform", 40)
     tt = TORCH[dtype]
     big = torch.zeros((w.M, 3 * w.K), dtype=tt, device="cuda")
@@ -432,12 +463,15 @@ def test_half_kept_tiles(dtype, b_r, pattern):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-def test_whole_tiles_as_16x16_blocks(dtype):
+@pytest.mark.parametrize("K,kernel", [(384, "k_linear16_split"), (352, "k_linear16")])
+def test_whole_tiles_as_16x16_blocks(dtype, K, kernel):
     """A 32 x 32 block mask written as 16 x 16 blocks (each kept block as its
     four quarters) keeps the same tiles with both halves: the two handles must
-    give the same output bits (GELU on, M = 300, DeiT-S fc1 shape)."""
-    w = wl.custom(92, 300, 1536, 384, 32, 32, dtype, "uniform", 50, gelu=True)
-    _, Y32 = run_bsr(w)
+    give the same output bits (GELU on, M = 300): the split kernel, which takes whole
+    tiles, and (K not a multiple of 64) the walk by halves against the one by tiles."""
+    w = wl.custom(92, 300, 1536, K, 32, 32, dtype, "uniform", 50, gelu=True)
+    h, Y32 = run_bsr(w)
+    assert kernels(lambda: lpv.bsr_linear(h, dev(w.X, dtype), None)) == {kernel}
     w16 = wl.Linear(w.name + ".as16", dtype, 16, 16, w.W, np.kron(w.mask, np.ones((2, 2), np.uint8)),
                     w.bias, True, w.X, w.M)
     _, Y16 = run_bsr(w16)
@@ -487,41 +521,48 @@ def _table_bytes(w):
     return total
 
 
+@pytest.mark.parametrize("M,kernel", [(300, "k_linear16_split"), (1665, "k_linear16")])
 @pytest.mark.parametrize("N,K,block", [(8192, 768, 32), (4096, 3072, 32), (8192, 768, 16)])
-def test_multi_launch_tables(N, K, block):
-    """Layers wide enough that the kernel's per-launch tables (walk, slot
+def test_multi_launch_tables(N, K, block, M, kernel):
+    """Layers wide enough that the persistent kernel's per-launch tables (walk, slot
     descriptors, bias) exceed the 32 KB it keeps in LDS: the call is split into
-    several launches over runs of output groups.  Sparse with GELU (also with
-    16 x 16 blocks, whose walk entries carry per-half row bits), and dense."""
-    w = wl.custom(75, 300, N, K, block, block, "bf16", "uniform", 50, gelu=True)
+    several launches over runs of output groups (few tokens take the split kernel, which
+    has no tables).  Sparse with GELU (also with 16 x 16 blocks, whose walk entries
+    carry per-half row bits), and dense."""
+    w = wl.custom(75, M, N, K, block, block, "bf16", "uniform", 50, gelu=True)
     assert _table_bytes(w) > 32 * 1024
-    say("multi-launch", N, K, block, "nnzb", w.nnzb)
-    _, Y = run_bsr(w)
-    assert_close(f64(Y), ref(w), "bf16", w.name)
+    say("multi-launch", N, K, block, "M", M, "nnzb", w.nnzb)
+    h, Y = run_bsr(w)
+    X, b, rows = dev(w.X, "bf16"), dev(w.bias, "bf16"), _sampled_rows(M, n=80, seed=5)
+    assert kernels(lambda: lpv.bsr_linear(h, X, b)) == {kernel}
+    assert_close(f64(Y)[rows], ref(w, w.X[rows]), "bf16", w.name)
     if block == 16:
         return
-    Yd = lpv.dense_linear(dev(w.W, "bf16"), dev(w.X, "bf16"), dev(w.bias, "bf16"), epi="gelu")
+    W = dev(w.W, "bf16")
+    Yd = lpv.dense_linear(W, X, b, epi="gelu")
     torch.cuda.synchronize()
-    r = oracle.linear(w.X, w.W, "bf16", 32, 32, np.ones_like(w.mask), w.bias, gelu=True)
-    assert_close(f64(Yd), r, "bf16", "dense " + w.name)
+    assert kernels(lambda: lpv.dense_linear(W, X, b)) == {kernel}
+    r = oracle.linear(w.X[rows], w.W, "bf16", 32, 32, np.ones_like(w.mask), w.bias, gelu=True)
+    assert_close(f64(Yd)[rows], r, "bf16", "dense " + w.name)
 
 
-@pytest.mark.parametrize("dense,block", [(False, 32), (False, 16), (True, 32)])
-def test_last_round_split(dense, block):
+@pytest.mark.parametrize("dense,block,sparsity", [(False, 32, 25), (False, 16, 50), (True, 32, 0)])
+def test_last_round_split(dense, block, sparsity):
     """38 token tiles x 12 output groups: with 256 compute units, 8 XCDs of 32
     workgroups, XCDs 0-5 own 5 token tiles (60 items: one whole round of 32
     and 28 left, too many to halve) and XCDs 6-7 own 4 (48 items: 16 left,
     each run as two half items).  Rows of tiles on both kinds of XCD are
-    checked against the oracle, for the block-sparse launch (32 x 32 blocks,
-    and 16 x 16 blocks, whose tiles are walked by 16-column halves) and the
-    dense one."""
-    w = wl.custom(78, 38 * 256, 3072, 768, block, block, "bf16", "uniform", 0 if dense else 50)
+    checked against the oracle, for the block-sparse launch (32 x 32 blocks, too many kept
+    for the kernel with X in registers, and 16 x 16 blocks, whose tiles are walked by
+    16-column halves) and the dense one."""
+    w = wl.custom(78, 38 * 256, 3072, 768, block, block, "bf16", "uniform", sparsity)
     say("last round split", "dense" if dense else "sparse", block, "M", w.M, "nnzb", w.nnzb)
     if dense:
         Y = lpv.dense_linear(dev(w.W, "bf16"), dev(w.X, "bf16"), dev(w.bias, "bf16"))
         torch.cuda.synchronize()
     else:
-        _, Y = run_bsr(w)
+        h, Y = run_bsr(w)
+        assert kernels(lambda: lpv.bsr_linear(h, dev(w.X, "bf16"), None)) == {"k_linear16"}
     g = np.random.default_rng(79)
     rows = []
     for tile in (0, 6, 7, 14, 30, 31, 37):
@@ -532,13 +573,21 @@ def test_last_round_split(dense, block):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-def test_zipf_many_token_tiles(dtype):
-    """Skewed (Zipf) row keep counts with more than 8 token tiles of 256, so the
-    XCD-owned item order of the persistent kernel runs with uneven groups."""
-    w = wl.custom(76, 8 * 256 + 77, 768, 384, 32, 32, dtype, "zipf", 40, gelu=True)
+@pytest.mark.parametrize("M,N,sparsity,kernel", [
+    (8 * 256 + 77, 768, 40, "k_linear16_split"),
+    (23 * 256 + 77, 1536, 40, "k_linear16"),  # 24 token tiles x 6 groups, 3 tiles to an XCD
+    (47 * 256 + 77, 1536, 15, "k_linear16"),  # 48: more than a round
+])
+def test_zipf_many_token_tiles(dtype, M, N, sparsity, kernel):
+    """Skewed (Zipf) row keep counts with more than 8 token tiles of 256: the
+    XCD-owned item order of the persistent kernel runs with uneven groups, and a
+    smaller product through the split kernel."""
+    w = wl.custom(76, M, N, 384, 32, 32, dtype, "zipf", sparsity, gelu=True)
     say("zipf", dtype, "M", w.M, "nnzb", w.nnzb)
-    _, Y = run_bsr(w)
-    assert_close(f64(Y), ref(w), dtype, w.name)
+    h, Y = run_bsr(w)
+    assert kernels(lambda: lpv.bsr_linear(h, dev(w.X, dtype), None)) == {kernel}
+    rows = np.arange(M) if M < 4096 else _sampled_rows(M, n=300, seed=6)
+    assert_close(f64(Y)[rows], ref(w, w.X[rows]), dtype, w.name)
 
 
 def test_full_b_stack_links_sampled():

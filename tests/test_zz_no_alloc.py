@@ -8,7 +8,7 @@ import torch
 
 import oracle
 import workloads as wl
-from gpu_util import TOL, assert_close, dev, f64, say
+from gpu_util import TOL, assert_close, dev, f64, kernels, say
 from paper_2407_02068_amd import lpv
 
 pytestmark = pytest.mark.gpu
@@ -30,7 +30,9 @@ def test_bias_grad_noalloc_two_calls(dtype):
 
 
 def test_bias_grad_noalloc_empty_and_columns_past_scratch_share():
-    # M = 0 gives zeros; N = 65536 (the largest N) caps the chunks at 16
+    # M = 0 gives zeros; N = 65536 (the largest N) caps the chunks at 16.  300 rows take
+    # one launch without a scratch; 4097 rows of integers, whose sums are exact in float32,
+    # the chunks
     out = torch.full((64,), 3.0, dtype=torch.bfloat16, device="cuda")
     lpv.bias_grad_noalloc(torch.empty((0, 64), dtype=torch.bfloat16, device="cuda"), out)
     torch.cuda.synchronize()
@@ -41,3 +43,9 @@ def test_bias_grad_noalloc_empty_and_columns_past_scratch_share():
     db = lpv.bias_grad_noalloc(Gd, torch.empty(N, dtype=torch.bfloat16, device="cuda"))
     torch.cuda.synchronize()
     assert_close(f64(db), oracle.grad_bias(G, "bf16"), "bf16", "noalloc N=65536")
+    del G, Gd
+    M = 4097
+    Gd = torch.randint(-4, 6, (M, N), dtype=torch.int8, device="cuda").to(torch.bfloat16)
+    db = torch.full((N,), 7.0, dtype=torch.bfloat16, device="cuda")
+    assert kernels(lambda: lpv.bias_grad_noalloc(Gd, db)) == {"k_bias_partial", "k_bias_reduce"}
+    assert torch.equal(db, Gd.sum(0, dtype=torch.float32).to(torch.bfloat16))
