@@ -142,8 +142,6 @@ def kernel_label(name):
     labels = (("k_linear_f32", "k_linear_f32 (linear, fp32)"),
               ("k_block_scores_lds<2, true", "k_block_scores_lds, Taylor (lpv_mask_topk)"),
               ("k_block_scores_lds<2, false", "k_block_scores_lds, sum of squares (lpv_mask_topk)"),
-              ("k_block_scores<2, true", "k_block_scores, Taylor (lpv_delta_curve)"),
-              ("k_block_scores<2, false", "k_block_scores, sum of squares (lpv_mask_topk)"),
               ("k_block_scores", "k_block_scores (lpv_mask_topk)"),
               ("k_delta_dots", "k_delta_dots (lpv_delta_curve)"),
               ("k_rank", "k_rank (lpv_mask_topk, lpv_delta_curve)"),

@@ -96,12 +96,15 @@ typedef struct {
  * The handle holds the canonical BSR arrays: row_ptr[R + 1] (row_ptr[0] = 0,
  * row_ptr[r + 1] - row_ptr[r] = kept blocks of block-row r), col_idx[nnzb]
  * (ascending within a block-row) and values[nnzb][b_r][b_c] (raw element bits
- * of each kept block, row-major), plus the tile schedule and an internal copy
- * of the kept values in matrix-core operand order.  Dropped blocks are never
- * read by lpv_bsr_linear, so NaN or Inf in them cannot reach Y.
+ * of each kept block, row-major), plus (bf16 / fp16) the tile schedule and an
+ * internal copy of the kept 32 x 32 tiles in matrix-core operand order; a second one by
+ * tile row where K <= 768 is a multiple of 64 and N <= 4096.  The schedule arrays are
+ * sized for a full mask, 28 bytes per 256 x 32 elements of the weight.  Dropped
+ * blocks are never read by lpv_bsr_linear, so NaN or Inf in them cannot reach Y.
  *
- * Allocates device memory (freed by lpv_bsr_destroy) and waits once on
- * `stream` to learn the kept count.  W and mask may be freed afterwards.
+ * Allocates device memory (freed by lpv_bsr_destroy) and waits on `stream`
+ * twice: to learn the kept count, and before it returns.  W and mask may be freed
+ * afterwards.
  * N, K <= 65536.  bf16 / fp16: at most 2^21 - 1 kept 32 x 32 tiles (the
  * kernels address the tile copy with 32-bit byte offsets) and K <= 63424 (a
  * group's walk, one entry per 32 reduction columns, must fit the kernel's LDS
@@ -167,8 +170,13 @@ lpv_status lpv_bsr_unpack(const lpv_bsr* h, void* W_out, int64_t ldw, void* stre
  * token tile times each group of output tile rows walks only the kept tiles
  * of its rows, on the matrix cores for bf16/fp16.  M = 0 is a no-op.
  * One kernel launch per run of output groups whose per-launch tables fit in
- * LDS (a single launch for ViT-sized layers), no allocation, no host
- * synchronisation.
+ * LDS (a single launch for ViT-sized layers; fp32: per 2^20 token tiles), no
+ * allocation, no host synchronisation.
+ * A call gives the same bits every time, and a row's do not depend on the other
+ * rows' values.  The order of a row's float32 sums depends on the weight and on M (the
+ * kernel is chosen by the size of the product), so the same row in calls of different M
+ * may differ in the last bits of those sums, rounded once; the same for
+ * lpv_dense_linear.
  * Errors: INVALID_ARG, SHAPE, ALIAS, HIP.
  */
 lpv_status lpv_bsr_linear(const lpv_bsr* h, const void* X, int64_t ldx, int64_t M,

@@ -13,10 +13,12 @@
 // workgroup and no last round.
 //
 // Bound: with few kept tiles the stores of Y and the read of X (50432 tokens, 768
-// -> 3072 at 90% block sparsity: 88 us for 387 MB; k_linear16 102); else the LDS
-// reads of W, whose round trip two waves per SIMD cover only in part (50%: 157 us,
-// k_linear16 172; 70%: 126 / 150).  12608 tokens, 384 -> 1536, 50%, GELU: 26.5 us
-// (32.4).  The stores were the bound throughout (121 us at any sparsity above
+// -> 3072 at 90% block sparsity: 88 us for 387 MB; k_linear16 102); else the round
+// trips of the LDS reads of W, which are waited for right after the two products they
+// run beside, and the row epilogues, at two waves per SIMD (50%: 157 us, k_linear16 172;
+// 70%: 126 / 150).  No unit is near its rate there: matrix cores 31% busy, LDS 28%, waves
+// 32% issuing and 43% waiting (24% at s_waitcnt).  12608 tokens, 384 -> 1536, 50%, GELU:
+// 26.5 us (32.4).  The stores were the bound throughout (121 us at any sparsity above
 // 70%) while each tile row wrote its own 64-byte halves of Y's 128-byte lines.
 // Two waves of 64 tokens per SIMD do not fit the registers, one does and ran no
 // faster (158 us): every LDS wait and every epilogue is then exposed.
