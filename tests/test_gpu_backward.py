@@ -179,6 +179,23 @@ def test_bias_grad_route(M, N, dtype, one, noalloc_one):
         assert torch.equal(db, torch.full_like(db, M))  # (rounded as the sum is)
 
 
+@pytest.mark.parametrize("M,N,dtype,groups", [
+    (4100, 32768, "bf16", 8), (4100, 30720, "f16", 32),   # 32 chunks, and 35
+    (4100, 16384, "f32", 8), (4100, 15360, "f32", 32),
+    (50000, 72, "bf16", 32),                              # 512
+])
+def test_bias_grad_reduction(M, N, dtype, groups):
+    # the chunks' sums added by 8 lane groups up to 32 chunks, by 32 above; integers, whose
+    # sums are exact in float32
+    G = torch.randint(-4, 5, (M, N), dtype=torch.int8, device="cuda").to(TORCH[dtype])
+    db = torch.full((N,), 7.0, dtype=G.dtype, device="cuda")
+    say("bias grad reduction", M, N, dtype)
+    for f in (lpv.bias_grad, lpv.bias_grad_noalloc):
+        names = kernels(lambda: f(G, db), args=True)
+        assert any(n.startswith("k_bias_reduce<") and n.endswith(", %d>" % groups) for n in names), names
+        assert torch.equal(db, G.sum(0, dtype=torch.float32).to(G.dtype))
+
+
 def test_backward_m0():
     w, G = case(4, 256, 256, 32, 32, "bf16", cfg=95)
     h = lpv.bsr_pack(dev(w.W, "bf16"), dev(w.mask), 32, 32)
