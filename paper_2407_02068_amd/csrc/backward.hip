@@ -812,14 +812,21 @@ hipError_t scratch_err[MAX_DEVICES];
 // chunks: bf16, 768 columns, 2048 rows 6.9 / 13.5, 4096 10.7 / 13.8; 3072 columns, 2048 rows
 // 12.0 / 14.4, 4096 20.7 / 15.3; 16384 columns, 1024 rows 9.8 / 15.8; 65536 columns, 2048 rows
 // 68 / 60, 4096 136 / 101; fp32, 768 columns, 2048 rows 8.2 / 9.3, 4096 18.1 / 9.7.  Without an
-// allocation that decides; with one the chunks' call takes 20 us more of host time, which
-// the kernels hide only when they are long.
+// allocation that decides, and with G in a cache, where the direct launch gains most (768
+// columns, 2048 rows 5.7 / 8.4) but not for fp32 rows past 2048 (64 columns, 4096 rows 6.1 /
+// 6.4, from memory 14.8 / 10.8) or with over 128 KiB of columns, thousands of workgroups
+// (65536 fp32, 64 rows 9.3 / 6.8).  With an allocation the chunks' call takes 20 us more of
+// host time, which the kernels hide only when they are long.
 static bool use_bias_direct(int64_t M, int64_t N, int dtype, bool alloc)
 {
-    const int64_t bytes = M * N * (dtype == LPV_F32 ? 4 : 2), MB = (int64_t)1 << 20;
+    const int64_t row = N * (dtype == LPV_F32 ? 4 : 2), MB = (int64_t)1 << 20;
     if (M > 4096)
         return false;
-    return bytes <= (alloc ? 128 * MB : M <= 2048 ? 32 * MB : 4 * MB);
+    if (alloc)
+        return M * row <= 128 * MB;
+    if (M > 2048)
+        return dtype != LPV_F32 && M * row <= 4 * MB;
+    return M * row <= 32 * MB && row <= MB / 8;
 }
 
 // One launch without a workspace (k_bias_direct), in place of the chunks.

@@ -167,6 +167,9 @@ def test_bias_grad_direct(M, N, dtype):
     (1024, 16384, "bf16", True, True),
     (1025, 16384, "bf16", True, False),
     (1025, 65536, "bf16", False, False), # and here all of them: 128 MiB
+    (2049, 64, "f32", True, False),      # fp32 rows past 2048
+    (64, 65536, "f32", True, False),     # over 128 KiB of columns
+    (64, 65536, "bf16", True, True),
 ])
 def test_bias_grad_route(M, N, dtype, one, noalloc_one):
     G = torch.ones((M, N), dtype=TORCH[dtype], device="cuda")
