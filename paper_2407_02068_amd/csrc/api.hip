@@ -234,7 +234,8 @@ lpv_status pack_weight(lpv::PackArgs a, int64_t N, int64_t K, int dt, int32_t b_
 
     // values, the tiles in operand order (and again by tile row) and col_idx, put together
     // where one allocation costs less than two (us to allocate and to free, by size:
-    // under 2 MiB 0.7 + 0.6, up to 4 MiB 11 + 12, up to 64 MiB 7 + 6, above 28 + 260)
+    // under 2 MiB 0.7 + 0.6, up to 4 MiB 11 + 12, up to 64 MiB 7 + 6, above 28 + 260): up to
+    // 2 MiB, and any to one of 2 MiB and more up to 64 MiB
     const size_t b_str = (size_t)h->n_tiles * lpv::TILE * lpv::TILE * es;
     const struct {
         void** at;
@@ -249,8 +250,7 @@ lpv_status pack_weight(lpv::PackArgs a, int64_t N, int64_t K, int dt, int32_t b_
     for (int i = 0; i < 4; ++i) {
         const size_t n = (parts[i].bytes + 511) / 512 * 512;  // (every part 512-byte aligned)
         int k = 0;
-        while (used[k] && !(used[k] + n < SMALL ||
-                            (used[k] >= SMALL && n >= SMALL && used[k] + n <= LARGE)))
+        while (used[k] && used[k] + n >= SMALL && (used[k] < SMALL || used[k] + n > LARGE))
             ++k;  // (ends at an empty one: at most a part in each before it)
         in[i] = k;
         off[i] = used[k];
